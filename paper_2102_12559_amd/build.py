@@ -13,7 +13,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libmsl.so")
-SOURCES = ["msl_capi.hip", "msl_aux.hip", "msl_stream.hip", "msl_mlp.hip", "msl_pond.hip"] + [
+SOURCES = ["msl_capi.hip", "msl_aux.hip", "msl_fields.hip", "msl_stream.hip", "msl_mlp.hip", "msl_pond.hip"] + [
     f"msl_stream_{t}{th}.hip" for t in ("f64", "f32", "f16", "bf16") for th in ("", "_th")]
 ARCH = os.environ.get("MSL_OFFLOAD_ARCH", "gfx950")
 FLAGS = ["-O3", f"--offload-arch={ARCH}", "-fPIC", "-std=c++20",

@@ -1,8 +1,8 @@
-// msl_aux.hip -- the kernels around the fused stream-and-collide: equilibrium
-// initialisation, ghost-layer fill (boundary rules), band conversion by lifting
-// and projection, refinement criterion and switching, class / band / tile
-// bookkeeping with an ordered compaction of the band cells, macroscopic
-// fields, population import/export and the deterministic FP64 reductions.
+// msl_aux.hip -- the kernels around the fused stream-and-collide: ghost-layer
+// fill (boundary rules), band conversion by lifting and projection, refinement
+// criterion and switching, class / band / tile bookkeeping with an ordered
+// compaction of the band cells, population import/export and the deterministic
+// FP64 reductions.
 #include "msl_band.hpp"
 #include "msl_device.hpp"
 
@@ -33,27 +33,6 @@ __device__ __forceinline__ void write_cell(const Tab *tab, const Geo &g, char *b
     store_pop<S>(p + (long long)i * g.plane, off, f[i], L.sc[i]);
     if (tab->thermal) store_pop<S>(p + (long long)(L.Q + i) * g.plane, off, gg[i], gs * L.sc[i]);
   }
-}
-
-// ---------------------------------------------------------------------------
-// initialisation: lattice equilibrium of each cell's own velocity set
-// ---------------------------------------------------------------------------
-template <typename S>
-__global__ void k_init_eq(const Tab *__restrict__ tab, Geo g, char *b0, char *b1,
-                          const uint8_t *__restrict__ cls, const double *__restrict__ rho,
-                          const double *__restrict__ u, const double *__restrict__ T) {
-  const long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= g.ncell) return;
-  int x, y, z;
-  cell_coords(g, k, x, y, z);
-  const int l = cls[k] & 1;
-  double uu[3] = {0, 0, 0};
-  for (int a = 0; a < g.dim; ++a) uu[a] = u[a * g.ncell + k];
-  const double Tk = (tab->thermal && T) ? T[k] : 1.0;
-  double f[MSL_MAXQ], gg[MSL_MAXQ];
-  cell_feq(tab->lat[l], g.dim, rho[k], uu, Tk, f);
-  for (int i = 0; i < tab->lat[l].Q; ++i) gg[i] = tab->gfac * Tk * f[i];
-  write_cell<S>(tab, g, l ? b1 : b0, l, g.idx(x, y, z), f, gg);
 }
 
 // ---------------------------------------------------------------------------
@@ -708,25 +687,8 @@ __global__ void __launch_bounds__(256) k_band_scatter(Geo g, const uint8_t *__re
 }
 
 // ---------------------------------------------------------------------------
-// macroscopic fields, population import / export
+// population import / export
 // ---------------------------------------------------------------------------
-template <typename S>
-__global__ void k_macros(const Tab *__restrict__ tab, Geo g, const char *bl, const char *bh,
-                         const uint8_t *__restrict__ cls, double *rho, double *u, double *T) {
-  const long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= g.ncell) return;
-  int x, y, z;
-  cell_coords(g, k, x, y, z);
-  const int l = cls[k] & 1;
-  double f[MSL_MAXQ], gg[MSL_MAXQ], r, uu[3], t;
-  read_cell<S>(tab, g, l ? bh : bl, l, g.idx(x, y, z), f, gg);
-  cell_macros(tab->lat[l], g.dim, tab->thermal, tab->cv, f, gg, r, uu, t);
-  if (rho) rho[k] = r;
-  if (u)
-    for (int a = 0; a < g.dim; ++a) u[a * g.ncell + k] = uu[a];
-  if (T) T[k] = t;
-}
-
 template <typename S>
 __global__ void k_pops(const Tab *__restrict__ tab, Geo g, char *base, int l, int fg,
                        const uint8_t *__restrict__ cls, double *out, const double *in) {
@@ -921,13 +883,6 @@ static inline unsigned nblocks(long long n) { return (unsigned)((n + AUX_BLOCK -
   } while (0)
 
 static inline int last_err() { return hipGetLastError() == hipSuccess ? MSL_OK : MSL_EHIP; }
-
-int msl_launch_init_eq(msl_ctx *c, const double *rho, const double *u, const double *T) {
-  char *b0 = c->planes[0][c->cur], *b1 = c->nlat > 1 ? c->planes[1][c->cur] : nullptr;
-  DISPATCH_STORE(c, k_init_eq, dim3(nblocks(c->ncell)), dim3(AUX_BLOCK), c->dtab, c->geo, b0, b1,
-                 c->cls, rho, u, T);
-  return last_err();
-}
 
 static void bc_args(const msl_ctx *c, BCArgs &b) {
   for (int f = 0; f < 6; ++f) {
@@ -1277,13 +1232,6 @@ int msl_launch_classify(msl_ctx *c) {
   hipLaunchKernelGGL(k_band_scan, dim3(3), dim3(1024), 0, c->stream, c->blk, c->nblk, c->bcount);
   hipLaunchKernelGGL(k_band_scatter, dim3(c->nblk), dim3(256), 0, c->stream, g, c->cls, c->blk,
                      c->nblk, c->blist[0], c->blist[1]);
-  return last_err();
-}
-
-int msl_launch_macros(msl_ctx *c, double *rho, double *u, double *T) {
-  DISPATCH_STORE(c, k_macros, dim3(nblocks(c->ncell)), dim3(AUX_BLOCK), c->dtab, c->geo,
-                 c->planes[0][c->cur], c->nlat > 1 ? c->planes[1][c->cur] : nullptr, c->cls, rho,
-                 u, T);
   return last_err();
 }
 

@@ -94,12 +94,15 @@ __device__ __forceinline__ int msl_xcd_tile(int b, int nb) {
   return xcd < rem ? xcd * (per + 1) + slot : rem * (per + 1) + (xcd - rem) * per + slot;
 }
 
-// interior coordinates of cell k (x fastest)
+// interior coordinates of cell k (x fastest); a grid holds fewer than 2^31
+// cells, so 32-bit divisions serve (64-bit ones are long instruction sequences)
 __device__ __forceinline__ void cell_coords(const Geo &g, long long k, int &x, int &y, int &z) {
-  x = (int)(k % g.nx);
-  k /= g.nx;
-  y = (int)(k % g.ny);
-  z = (int)(k / g.ny);
+  const unsigned kk = (unsigned)k, nx = (unsigned)g.nx, ny = (unsigned)g.ny;
+  const unsigned r = kk / nx;
+  x = (int)(kk - r * nx);
+  const unsigned zz = r / ny;
+  y = (int)(r - zz * ny);
+  z = (int)zz;
 }
 
 template <typename S>
