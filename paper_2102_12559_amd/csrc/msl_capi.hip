@@ -124,6 +124,10 @@ static void build_lat(LatTab &L, int n, int dim, const ld *x, const ld *w, doubl
     L.cr[a] = (double)x[a];
     L.w[a] = (double)w[a];
     L.wf[a] = (float)w[a];
+    ld den = 1.0L;
+    for (int b = 0; b < n; ++b)
+      if (b != a) den *= x[a] - x[b];
+    L.den[a] = (double)(1.0L / den);
     ld fact = 1.0L;
     for (int j = 0; j < n; ++j) {
       if (j > 0) fact *= (ld)j;
@@ -239,7 +243,7 @@ struct Layout {
   size_t off_tab, off_planes[2], off_cls, off_newmask, off_tflag, off_blist[2], off_bcount, off_blk,
       off_red, off_flag, off_tlist, off_kn, off_pond, off_mlp, total;
   int nblk, Q[2], np[2];
-  long long plane_bytes;
+  long long plane_bytes, pond_nslot;
   int mlpF, mlpO, mlpH, mlpP, nctile, nct[3];
   size_t mlp_off[12];
 };
@@ -307,9 +311,14 @@ static void make_layout(const msl_config *cfg, Layout &L) {
   if (cfg->crit_kind == MSL_CRIT_KN && nl > 1) off = align256(off + (size_t)g.ncell * 2 * 8);
   // co-moving frames: two buffers of populations and frames, iteration counters
   L.off_pond = off;
-  // (then the wall densities of the two y faces, 2 nx doubles)
-  if (cfg->pond)
-    off = align256(off + (size_t)g.ncell * 8 * 2 * (L.np[0] + (nl > 1 ? L.np[1] : 0) + 4) + 64 + (size_t)16 * g.nx);
+  // (then the wall densities of the two y faces, 2 nx doubles, and the pass
+  // counts of the step's workgroups)
+  if (cfg->pond) {
+    L.pond_nslot = (long long)((g.nx + MSL_POND_SLOT_X - 1) / MSL_POND_SLOT_X) *
+                   ((g.ny + MSL_POND_SLOT_Y - 1) / MSL_POND_SLOT_Y);
+    off = align256(off + (size_t)g.ncell * 8 * 2 * (L.np[0] + (nl > 1 ? L.np[1] : 0) + 4) + 64 + (size_t)16 * g.nx +
+                   (size_t)16 * L.pond_nslot);
+  }
   // learned closure
   if (cfg->lift_mode == MSL_LIFT_MLP && nl > 1) {
     const int q = L.Q[0], Q = L.Q[1];
@@ -524,6 +533,8 @@ int msl_create(const msl_config *cfg, void *ws, size_t bytes, void *stream, msl_
     c->pond_fr[1] = pb + nfr;
     c->pond_stats = (unsigned long long *)(pb + 2 * nfr);
     c->pond_wall = pb + 2 * nfr + 8;
+    c->pond_slots = (unsigned long long *)(c->pond_wall + 2 * L.geo.nx);
+    c->pond_nslot = L.pond_nslot;
   }
   c->tcount = c->tlist + (size_t)L.geo.ntx * L.geo.nty * L.geo.ntz;
   if (L.mlpP) {
@@ -771,7 +782,7 @@ int msl_profile_read(msl_ctx *c, double *stats) {
 // positivity flags are read once at the end of the call
 static int pond_step(msl_ctx *c, int nsteps) {
   if (hipMemsetAsync(c->flag, 0, sizeof(int), c->stream) != hipSuccess ||
-      hipMemsetAsync(c->pond_stats, 0, 16, c->stream) != hipSuccess)
+      hipMemsetAsync(c->pond_slots, 0, 16 * (size_t)c->pond_nslot, c->stream) != hipSuccess)
     return MSL_EHIP;
   for (int s = 0; s < nsteps; ++s) {
     const int rc = msl_pond_launch_step(c);
@@ -798,6 +809,7 @@ int msl_pond_frames(msl_ctx *c, double *out) {
 int msl_pond_iterations(msl_ctx *c, double *mean, int *max) {
   if (!c || !c->cfg.pond) return MSL_EINVAL;
   unsigned long long h[2] = {0, 0};
+  if (msl_pond_launch_stats(c) != MSL_OK) return MSL_EHIP;
   if (hipMemcpyAsync(h, c->pond_stats, sizeof(h), hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
       hipStreamSynchronize(c->stream) != hipSuccess)
     return MSL_EHIP;

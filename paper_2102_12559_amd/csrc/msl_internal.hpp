@@ -27,6 +27,7 @@
 struct LatTab {
   int n, Q;
   double cr[MSL_MAXN], w[MSL_MAXN];
+  double den[MSL_MAXN];            // 1 / prod_{b != a} (c_a - c_b)
   double hw[MSL_MAXN][MSL_MAXN];   // w_a He_j(c_a) / j!
   double v[3][MSL_MAXN];           // particle velocity of node a along axis
   int n0[3][MSL_MAXN];
@@ -143,11 +144,12 @@ struct msl_ctx {
   uint8_t *newmask;
   double *kn_rho, *kn_lam;   // Knudsen-number criterion: density and mean free path per cell
   // co-moving frames: populations [NP][ncell] of each velocity set and
-  // buffer ([set][buffer]) and frames [4][ncell] of each buffer; stats:
-  // iteration sum (u64), then maximum (int)
+  // buffer ([set][buffer]) and frames [4][ncell] of each buffer; slots: pass
+  // sum and maximum of every workgroup of the step launch; stats: their total
   double *pond_f[2][2], *pond_fr[2];
   double *pond_wall;      // diffuse y walls: wall density per column [2][nx] (low, high face)
-  unsigned long long *pond_stats;
+  unsigned long long *pond_stats, *pond_slots;
+  long long pond_nslot;
   long long pond_cells_steps;
   uint8_t *tflag;         // per micro-tile: bit0 has low cells, bit1 has high cells
   int *blist[2];          // band cells of each order, ascending cell index
@@ -236,6 +238,9 @@ int msl_launch_conservation(msl_ctx *c, double *dev_out5);
 int msl_pond_launch_init(msl_ctx *c, const double *rho, const double *u, const double *T);
 int msl_pond_launch_macros(msl_ctx *c, double *rho, double *u, double *T);
 int msl_pond_launch_step(msl_ctx *c);
+int msl_pond_launch_stats(msl_ctx *c);
+#define MSL_POND_SLOT_X 4   // cells of the narrowest step workgroup along x and y
+#define MSL_POND_SLOT_Y 4
 // co-moving frames, two sets: cells whose set differs from `mask` convert their
 // own state in their own frame (convert = 0: only the sets change), then the
 // band is rebuilt and converted

@@ -3,22 +3,21 @@
 //
 // Every cell keeps its post-collision populations in its own frame
 // lambda = {u, T} (eq. reference; particle velocities sqrt(T) c_i + u, eq. vi,
-// with T_L = 1).  A group of GS lanes (GS = the power of two >= Q) owns one
-// cell, one lane per population; a workgroup's cells are one x segment of a
-// row, and the 5-row neighbourhood of the segment (populations and frames,
-// boundary rules applied) is staged in LDS once.  Per iteration of the
-// predictor-corrector:
-// each lane finds its population's departure point x - v_i dt in the current
+// with T_L = 1).  A group of lanes owns one cell, one lane per x node of the
+// velocity set; a workgroup's cells are an x segment of four rows, and the
+// neighbourhood of the tile (populations and frames, boundary rules applied)
+// is staged in LDS once.  Per iteration of the predictor-corrector:
+// each lane finds its populations' departure points x - v_i dt in the current
 // frame, and for each of the 3 x 3 collocation points around the nearest node
 // transfers that point's population vector from its own frame to the current
-// one and keeps its own component (eqs. reconstructionPond, fll).  The
+// one and keeps its own components (eqs. reconstructionPond, fll).  The
 // transfer G = M_target^{-1} M_source of the moment matrices of eq. momf
 // factorises per axis, and its one-axis factor is the Lagrange basis of the
 // lattice nodes evaluated at the source nodes mapped into the target frame:
 //   G_x[a][a'] = l_a((sqrt(T_s) c_a' + u_s,x - u_x) / sqrt(T)),
 // because the inverse of a Vandermonde matrix holds the Lagrange basis
 // polynomials of its nodes.  The group then sums rho, j, E of the
-// reconstructed populations (shuffles within the group), which define the
+// reconstructed populations (shuffles over the cell's lanes), which define the
 // next frame (eqs. correctorfields), until neither a velocity component nor T
 // changes by more than 1e-14 (at most 60 passes).  The collision runs in the
 // converged frame, where f^eq = rho W_i and g^eq = (cv - 1) T rho W_i (eqs.
@@ -46,23 +45,82 @@ struct PondArgs {
   double st[4][5];   // fixed-equilibrium face states rho, ux, uy, uz, T
 };
 
-template <int GS>
-__device__ __forceinline__ double group_sum(double v) {
+// sum over a cell's lanes (CW apart within the wave)
+template <int CW>
+__device__ __forceinline__ double cell_sum(double v) {
 #pragma unroll
-  for (int o = GS / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, GS);
+  for (int o = CW; o < 64; o <<= 1) v += __shfl_xor(v, o);
   return v;
 }
 
-template <int N, bool TH>
+// Lane layout of the step kernel.  A cell has GS lanes, one per x node a of its
+// velocity set (GS = 4 or 8; lanes with a >= N idle), each of which carries the
+// populations (a, b) of every y node b.  The stencil of a population is the
+// product of an x offset that depends on a alone and a y offset that depends
+// on b alone, so the transfer along x of a collocation point's populations is
+// done once per (point, a) and shared by the y nodes, and the y rows of the
+// transfer come from shared partial products.  (One lane per population, which
+// repeats both for every population, issued about seven times the
+// instructions.)  SPX: the three point columns of a stencil go to lanes of
+// their own as well (16 lanes per cell, 3 N of them at work), whose partial
+// populations are added once the frame has converged; the sums that define the
+// next frame are linear, so they need no such step.  A third of the serial
+// work per lane, for grids that leave the chip idle, and a better fit of
+// N = 5 (15 of 16 lanes against 5 of 8).  A wave holds one row segment of CW
+// cells, node-major (lane = index CW + cell), a workgroup four rows of it.
+template <int N, bool TH, bool SPX>
 struct PondTraits {
   static constexpr int Q = N * N;
   static constexpr int NP = TH ? 2 * Q : Q;
-  static constexpr int GS = Q <= 16 ? 16 : (Q <= 32 ? 32 : 64);
-  static constexpr int TW = 256 / GS;         // cells of a workgroup: one x segment of a row
-  static constexpr int SW = TW + 4;           // staged columns (two on each side)
-  static constexpr int SP = SW * 5;           // staged collocation points (five rows)
-  static constexpr int STRIDE = NP + 4;       // doubles per staged point: populations, frame
+  static_assert(!SPX || 3 * N <= 16, "16 lanes per cell");
+  static constexpr int GS = SPX ? 16 : (N <= 4 ? 4 : 8);   // lanes per cell
+  static constexpr int PTS = SPX ? 1 : 3;     // point columns per lane
+  static constexpr int CW = 64 / GS;          // cells of a wave: one x segment of a row
+  static constexpr int TY = 4;                // rows of a workgroup
+  static constexpr int SW = CW + 4;           // staged columns (two on each side)
+  static constexpr int SP = SW * (TY + 4);    // staged collocation points
+  // doubles per staged point: populations, frame velocity, sqrt of its
+  // temperature; an odd number of 16-byte units, so that 16 consecutive points
+  // start in different LDS banks
+  static constexpr int EV = (NP + 3 + 1) / 2 * 2;
+  static constexpr int STRIDE = EV / 2 % 2 ? EV : EV + 2;
 };
+
+// unnormalised Lagrange basis at z: l[b] = prod_{c != b} (z - x_c), from shared
+// products of pairs
+template <int N>
+__device__ __forceinline__ void lagrange_products(double z, const double *xn, double *l) {
+  double d[N];
+#pragma unroll
+  for (int m = 0; m < N; ++m) d[m] = z - xn[m];
+  if constexpr (N == 3) {
+    l[0] = d[1] * d[2];
+    l[1] = d[0] * d[2];
+    l[2] = d[0] * d[1];
+  } else if constexpr (N == 4) {
+    const double p = d[0] * d[1], q = d[2] * d[3];
+    l[0] = d[1] * q;
+    l[1] = d[0] * q;
+    l[2] = d[3] * p;
+    l[3] = d[2] * p;
+  } else if constexpr (N == 5) {
+    const double p = d[0] * d[1], q = d[2] * d[3], p4 = p * d[4], q4 = q * d[4];
+    l[0] = d[1] * q4;
+    l[1] = d[0] * q4;
+    l[2] = d[3] * p4;
+    l[3] = d[2] * p4;
+    l[4] = p * q;
+  } else {
+    static_assert(N == 6, "velocity sets of 3 to 6 nodes per axis");
+    const double p = d[0] * d[1], q = d[2] * d[3], r = d[4] * d[5], qr = q * r, pr = p * r, pq = p * q;
+    l[0] = d[1] * qr;
+    l[1] = d[0] * qr;
+    l[2] = d[3] * pr;
+    l[3] = d[2] * pr;
+    l[4] = d[5] * pq;
+    l[5] = d[4] * pq;
+  }
+}
 
 // the collocation point (x, y) (possibly outside the domain): the cell index
 // whose state it takes, -1 - face for a fixed-equilibrium face state, or
@@ -80,29 +138,54 @@ __device__ __forceinline__ long long pond_resolve(const PondArgs &pa, int x, int
   return (long long)y * pa.nx + x;
 }
 
-template <int N, bool TH, bool QE>
+// Bound by FP64 issue (the VALU issues about 70 % of the time).  A step of
+// 1024^2 thermal D2Q16, 3 passes: 6.7 ms with one lane per population and
+// pass counts by atomics, 0.80 ms now; 512^2: 1692 us, 225 us now (432 us with
+// the atomics).  The 4096 x 4 two-set shock, bound by latency: 139 and 122 us
+// for its D2Q16 and D2Q25 launches, 29 and 45 us now.
+template <int N, bool TH, bool QE, bool SPX>
 __global__ void __launch_bounds__(256)
 k_pond_step(const Tab *__restrict__ tab, int lat, const uint8_t *__restrict__ cls, PondArgs pa,
             const double *__restrict__ fin, const double *__restrict__ frin, double *__restrict__ fout,
-            double *__restrict__ frout, int *__restrict__ flag, unsigned long long *__restrict__ itsum,
-            int *__restrict__ itmax, const double *__restrict__ wrho) {
-  using Tr = PondTraits<N, TH>;
-  constexpr int Q = Tr::Q, NP = Tr::NP, GS = Tr::GS, TW = Tr::TW, SW = Tr::SW, SP = Tr::SP,
-                STRIDE = Tr::STRIDE;
-  // the workgroup's cells: x in [x0, x0 + TW) of row y; their collocation
-  // points lie within two cells, so the SW x 5 points around the segment
-  // (populations and frames, boundary rules applied) are staged in LDS once
-  __shared__ double stg[SP * STRIDE];
+            double *__restrict__ frout, int *__restrict__ flag, unsigned long long *__restrict__ stats,
+            const double *__restrict__ wrho) {
+  using Tr = PondTraits<N, TH, SPX>;
+  constexpr int Q = Tr::Q, NP = Tr::NP, PTS = Tr::PTS, CW = Tr::CW, SW = Tr::SW, SP = Tr::SP, STRIDE = Tr::STRIDE;
+  __shared__ __align__(16) double stg[SP * STRIDE];
+  __shared__ int wstat[Tr::TY][2];
   const LatTab &L = tab->lat[lat];
-  const int x0 = blockIdx.x * TW, y = blockIdx.y;
+  const int x0 = blockIdx.x * CW, y0 = blockIdx.y * Tr::TY;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  // the lane's cell, x node and (SPX) point column
+  const int c = lane % CW, li = lane / CW;
+  const int a = SPX ? li % N : li, col = SPX ? (li / N < 3 ? li / N : 0) : 0;
+  const int px = x0 + c, py = y0 + w;
+  const bool inside = px < pa.nx && py < pa.ny;
+  const long long k = inside ? (long long)py * pa.nx + px : 0;
+  // cells of this launch's velocity set (with two sets); a tile without any
+  // leaves before it stages its neighbourhood
+  const bool cell_ok = inside && (cls[k] & 1) == lat;
+  if (!__syncthreads_or(cell_ok)) return;
   const double dt = tab->dt, cv = tab->cv;
-  for (int e = threadIdx.x; e < SP * STRIDE; e += 256) {
-    const int sp = e / STRIDE, m = e - sp * STRIDE;
-    const int sx = x0 - 2 + sp % SW, sy = y - 2 + sp / SW;
-    const long long q = pond_resolve(pa, sx, sy);
-    double v;
+  // the collocation points around the tile, two on every side (populations and
+  // frames, boundary rules applied): a thread takes one point, so that
+  // neighbouring threads read neighbouring cells of a plane
+  constexpr int NG = 256 / SP;
+  static_assert(NG >= 1, "one staged point per thread");
+  static_assert(CW >= MSL_POND_SLOT_X && Tr::TY == MSL_POND_SLOT_Y, "a statistics slot per workgroup");
+  if ((int)threadIdx.x < NG * SP) {
+    const int sp = threadIdx.x % SP, m0 = threadIdx.x / SP;
+    const long long q = pond_resolve(pa, x0 - 2 + sp % SW, y0 - 2 + sp / SW);
+    double *dst = stg + sp * STRIDE;
     if (q >= 0) {
-      v = m < NP ? fin[(long long)m * pa.ncell + q] : frin[(long long)(m - NP) * pa.ncell + q];
+#pragma unroll
+      for (int m = 0; m < NP; m += NG)
+        if (m + m0 < NP) dst[m + m0] = fin[(long long)(m + m0) * pa.ncell + q];
+      if (m0 == 0) {
+        dst[NP] = frin[q];
+        dst[NP + 1] = frin[pa.ncell + q];
+        dst[NP + 2] = sqrt(frin[3 * pa.ncell + q]);
+      }
     } else {
       // a fixed-equilibrium face state, or a diffuse wall point at the wall
       // state with the column's wall density: rho W_i (and (cv - 1) T rho W_i)
@@ -112,37 +195,46 @@ k_pond_step(const Tab *__restrict__ tab, int lat, const uint8_t *__restrict__ cl
       const double *st = wall ? pa.st[wi < pa.nx ? 2 : 3] : pa.st[-1 - q];
       const double rs = wall ? wrho[wi] : st[0];
       const double Ts = TH ? st[4] : 1.0;
-      const int j = m % Q;
-      const double fj = rs * L.w[j % N] * L.w[j / N];
-      if (m < Q) v = fj;
-      else if (m < NP) v = (cv - 1.0) * Ts * fj;
-      else v = m - NP == 0 ? st[1] : (m - NP == 1 ? st[2] : (m - NP == 2 ? 0.0 : Ts));
+      for (int m = m0; m < NP; m += NG) {
+        const int j = m % Q;
+        dst[m] = (m < Q ? 1.0 : (cv - 1.0) * Ts) * rs * L.w[j % N] * L.w[j / N];
+      }
+      if (m0 == 0) {
+        dst[NP] = st[1];
+        dst[NP + 1] = st[2];
+        dst[NP + 2] = sqrt(Ts);
+      }
     }
-    stg[e] = v;
   }
   __syncthreads();
-  const int c = threadIdx.x / GS, li = threadIdx.x % GS;
-  const int px = x0 + c, py = y;
-  const long long k = (long long)py * pa.nx + (px < pa.nx ? px : 0);
-  // cells of this launch's velocity set (with two sets)
-  const bool cell_ok = px < pa.nx && (cls[k] & 1) == lat;
-  const bool act = cell_ok && li < Q;
-  const int i = act ? li : 0, a = i % N, b = i / N;
-  // lattice nodes and the Lagrange denominators 1 / prod_{c != a} (x_a - x_c)
-  double xn[N], den[N];
-#pragma unroll
-  for (int m = 0; m < N; ++m) xn[m] = L.cr[m];
+  const bool act = cell_ok && (SPX ? li < 3 * N : li < N);   // lanes at work
+  const bool own_f = cell_ok && li < N;                      // lanes that write populations
+  // lattice nodes; the lane's node, the other nodes, and the Lagrange
+  // denominators 1 / prod_{c != a} (x_a - x_c)
+  double xn[N], den[N], xo[N - 1], xa = L.cr[0], wa = L.w[0], dena = L.den[0];
 #pragma unroll
   for (int m = 0; m < N; ++m) {
-    double p = 1.0;
-#pragma unroll
-    for (int cc = 0; cc < N; ++cc)
-      if (cc != m) p *= xn[m] - xn[cc];
-    den[m] = 1.0 / p;
+    xn[m] = L.cr[m];
+    den[m] = L.den[m];
   }
-  const double *own = stg + ((2) * SW + (c + 2)) * STRIDE + NP;
-  double ux = own[0], uy = own[1], T = own[3];
-  double ft = 0.0, gt = 0.0, rho = 0.0, Tn = 1.0;
+#pragma unroll
+  for (int m = 0; m < N - 1; ++m) xo[m] = a <= m ? xn[m + 1] : xn[m];
+#pragma unroll
+  for (int m = 1; m < N; ++m)
+    if (a == m) {
+      xa = xn[m];
+      wa = L.w[m];
+      dena = den[m];
+    }
+  const double *own = stg + ((w + 2) * SW + c + 2) * STRIDE;
+  double ux = inside ? frin[k] : 0.0, uy = inside ? frin[pa.ncell + k] : 0.0,
+         T = inside ? frin[3 * pa.ncell + k] : 1.0;
+  double ft[N], gt[TH ? N : 1], rho = 0.0, Tn = 1.0;
+#pragma unroll
+  for (int b = 0; b < N; ++b) {
+    ft[b] = 0.0;
+    if (TH) gt[TH ? b : 0] = 0.0;
+  }
   bool done = !cell_ok;
   int it = 0;
   for (int pass = 1; pass <= POND_MAXIT; ++pass) {
@@ -150,69 +242,142 @@ k_pond_step(const Tab *__restrict__ tab, int lat, const uint8_t *__restrict__ cl
     if (!done) {
       it = pass;
       const double sT = sqrt(T), isT = 1.0 / sT;
-      const double vx = sT * xn[a] + ux, vy = sT * xn[b] + uy;
-      const double dx = -vx * dt, dy = -vy * dt;
-      const int nx0 = (int)floor(dx + 0.5), ny0 = (int)floor(dy + 0.5);
-      const bool out = nx0 < -1 || nx0 > 1 || ny0 < -1 || ny0 > 1;
+      const double vx = sT * xa + ux, dx = -vx * dt;
+      const int nx0 = (int)floor(dx + 0.5);
+      bool out = nx0 < -1 || nx0 > 1;
+      const double xi = dx - nx0;
+      // 3-point Lagrange weights through -1, 0, 1, with the denominator of the
+      // lane's transfer row
+      const double w3[3] = {dena * (0.5 * xi * (xi - 1.0)), dena * (1.0 - xi * xi), dena * (0.5 * xi * (xi + 1.0))};
+      double wx[PTS];
+#pragma unroll
+      for (int m = 0; m < PTS; ++m) wx[m] = SPX ? (col == 0 ? w3[0] : (col == 1 ? w3[1] : w3[2])) : w3[m];
+      int ny0[N];
+      double yi[N];
+#pragma unroll
+      for (int b = 0; b < N; ++b) {
+        const double dy = -(sT * xn[b] + uy) * dt;
+        ny0[b] = (int)floor(dy + 0.5);
+        yi[b] = dy - ny0[b];
+        out |= ny0[b] < -1 || ny0[b] > 1;
+      }
       if (act && out) atomicOr(flag, 1);
       // (a lane whose stencil left the reach reads the nearest staged points
       // instead; its cell is reported and its result is not used)
-      const int ox = out ? 0 : nx0, oy = out ? 0 : ny0;
-      const double xi = dx - nx0, yi = dy - ny0;
-      // 3-point Lagrange weights through -1, 0, 1
-      const double wx[3] = {0.5 * xi * (xi - 1.0), 1.0 - xi * xi, 0.5 * xi * (xi + 1.0)};
-      const double wy[3] = {0.5 * yi * (yi - 1.0), 1.0 - yi * yi, 0.5 * yi * (yi + 1.0)};
-      double accf = 0.0, accg = 0.0;
-      for (int sy = -1; sy <= 1; ++sy)
-        for (int sx = -1; sx <= 1; ++sx) {
-          const double *pt = stg + ((oy + sy + 2) * SW + (c + 2 + ox + sx)) * STRIDE;
-          const double usx = pt[NP], usy = pt[NP + 1], Ts = pt[NP + 3];
-          // the transfer's rows of this lane's nodes a (x) and b (y)
-          const double sTs = sqrt(Ts);
-          double gx[N], gy[N];
+      const int ox = nx0 < -1 ? -1 : (nx0 > 1 ? 1 : nx0);
 #pragma unroll
-          for (int m = 0; m < N; ++m) {
-            const double zx = (sTs * xn[m] + usx - ux) * isT, zy = (sTs * xn[m] + usy - uy) * isT;
-            double px_ = den[a], py_ = den[b];
-#pragma unroll
-            for (int cc = 0; cc < N; ++cc) {
-              if (cc != a) px_ *= zx - xn[cc];
-              if (cc != b) py_ *= zy - xn[cc];
-            }
-            gx[m] = px_;
-            gy[m] = py_;
-          }
-          double vf = 0.0, vg = 0.0;
-#pragma unroll
-          for (int mb = 0; mb < N; ++mb) {
-            double sf = 0.0, sg = 0.0;
-#pragma unroll
-            for (int ma = 0; ma < N; ++ma) {
-              const int j = ma + N * mb;
-              sf += gx[ma] * pt[j];
-              if (TH) sg += gx[ma] * pt[Q + j];
-            }
-            vf += gy[mb] * sf;
-            if (TH) vg += gy[mb] * sg;
-          }
-          const double w = wx[sx + 1] * wy[sy + 1];
-          accf += w * vf;
-          if (TH) accg += w * vg;
-        }
-      ft = accf;
-      gt = TH ? accg : 0.0;
-      if (act) {
-        r = ft;
-        jx = vx * ft;
-        jy = vy * ft;
-        e = 0.5 * (vx * vx + vy * vy) * ft + gt;
+      for (int b = 0; b < N; ++b) {
+        ny0[b] = ny0[b] < -1 ? -1 : (ny0[b] > 1 ? 1 : ny0[b]);
+        ft[b] = 0.0;
+        if (TH) gt[TH ? b : 0] = 0.0;
       }
+#pragma unroll 1
+      for (int sr = -2; sr <= 2; ++sr) {
+        // the y weights of this row of points for every node b (zero outside
+        // its stencil); rows that no lane of the wave needs are left out
+        bool use = false;
+        double wy[N];
+#pragma unroll
+        for (int b = 0; b < N; ++b) {
+          const int s = sr - ny0[b];
+          const bool in = s >= -1 && s <= 1;
+          const double w0 = 1.0 - yi[b] * yi[b], w1 = 0.5 * yi[b] * (yi[b] + (double)s);
+          use |= in;
+          wy[b] = in ? (s == 0 ? w0 : w1) : 0.0;
+        }
+        if (!__any(use)) continue;
+        double vf[N], vg[TH ? N : 1];
+#pragma unroll
+        for (int b = 0; b < N; ++b) {
+          vf[b] = 0.0;
+          if (TH) vg[TH ? b : 0] = 0.0;
+        }
+        const double *prow = own + (sr * SW + ox - 1 + col) * STRIDE;
+        // the lane's points of the row, their populations read one y node ahead
+        // of their use: with three waves per SIMD the LDS latency is otherwise
+        // exposed at every node (the scheduling barriers keep the reads there)
+        double cf[N], cg[TH ? N : 1], nf[N], ng[TH ? N : 1], fr[3];
+        auto read = [&](int st, double (&f)[N], double (&g)[TH ? N : 1]) {
+          const double *pt = prow + st / N * STRIDE + st % N * N;
+#pragma unroll
+          for (int ma = 0; ma < N; ++ma) {
+            f[ma] = pt[ma];
+            if (TH) g[TH ? ma : 0] = pt[Q + ma];
+          }
+        };
+#pragma unroll
+        for (int m = 0; m < 3; ++m) fr[m] = prow[NP + m];
+        read(0, cf, cg);
+        double s = 0.0, by = 0.0, gx[N];
+#pragma unroll
+        for (int st = 0; st < PTS * N; ++st) {
+          const int sx = st / N, mb = st % N;
+          if (mb == 0) {
+            // the point's nodes in the current frame: z = s x + (u_s - u) / sqrt(T),
+            // and the x row of the lane's node a
+            s = fr[2] * isT;
+            by = (fr[1] - uy) * isT;
+            const double bx = (fr[0] - ux) * isT;
+#pragma unroll
+            for (int m = 0; m < N; ++m) {
+              const double z = s * xn[m] + bx;
+              double p = wx[sx] * (z - xo[0]);
+#pragma unroll
+              for (int cc = 1; cc < N - 1; ++cc) p *= z - xo[cc];
+              gx[m] = p;
+            }
+          }
+          if (st + 1 < PTS * N) read(st + 1, nf, ng);
+          if (mb == N - 2 && sx < PTS - 1) {
+#pragma unroll
+            for (int m = 0; m < 3; ++m) fr[m] = prow[(sx + 1) * STRIDE + NP + m];
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          double sf = 0.0, sg = 0.0;
+#pragma unroll
+          for (int ma = 0; ma < N; ++ma) {
+            sf += gx[ma] * cf[ma];
+            if (TH) sg += gx[ma] * cg[TH ? ma : 0];
+          }
+          double gy[N];   // the y rows of every node at the point's node mb
+          lagrange_products<N>(s * xn[mb] + by, xn, gy);
+#pragma unroll
+          for (int b = 0; b < N; ++b) {
+            vf[b] += gy[b] * sf;
+            if (TH) vg[TH ? b : 0] += gy[b] * sg;
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int ma = 0; ma < N; ++ma) {
+            cf[ma] = nf[ma];
+            if (TH) cg[TH ? ma : 0] = ng[TH ? ma : 0];
+          }
+        }
+#pragma unroll
+        for (int b = 0; b < N; ++b) {
+          ft[b] += wy[b] * vf[b];
+          if (TH) gt[TH ? b : 0] += wy[b] * vg[TH ? b : 0];
+        }
+      }
+#pragma unroll
+      for (int b = 0; b < N; ++b) {
+        ft[b] *= den[b];
+        if (TH) gt[TH ? b : 0] *= den[b];
+        if (act) {
+          const double vy = sT * xn[b] + uy;
+          r += ft[b];
+          jy += vy * ft[b];
+          e += 0.5 * (vx * vx + vy * vy) * ft[b];
+          if (TH) e += gt[TH ? b : 0];
+        }
+      }
+      jx = vx * r;
     }
-    // corrector: the group's sums (every lane of the wave takes part)
-    r = group_sum<GS>(r);
-    jx = group_sum<GS>(jx);
-    jy = group_sum<GS>(jy);
-    e = group_sum<GS>(e);
+    // corrector: the cell's sums (every lane of the wave takes part)
+    r = cell_sum<CW>(r);
+    jx = cell_sum<CW>(jx);
+    jy = cell_sum<CW>(jy);
+    e = cell_sum<CW>(e);
     if (!done) {
       const double nux = jx / r, nuy = jy / r;
       const double nT = TH ? (e / r - 0.5 * (nux * nux + nuy * nuy)) / cv : 1.0;
@@ -234,39 +399,116 @@ k_pond_step(const Tab *__restrict__ tab, int lat, const uint8_t *__restrict__ cl
     }
     if (__all(done)) break;
   }
+  if constexpr (SPX) {
+    // the three point columns' parts of each population
+#pragma unroll
+    for (int b = 0; b < N; ++b) {
+      ft[b] += __shfl(ft[b], lane + N * CW) + __shfl(ft[b], lane + 2 * N * CW);
+      if (TH) gt[TH ? b : 0] += __shfl(gt[TH ? b : 0], lane + N * CW) + __shfl(gt[TH ? b : 0], lane + 2 * N * CW);
+    }
+  }
   // collision in the converged frame {ux, uy, T}
   double tl = tab->tau;
   if (tab->tau_mode == 1) tl = tab->mu_ref * pow(Tn / tab->tau_ref_T, tab->mu_exp) / (rho * Tn * dt) + 0.5;
-  const double om = 1.0 / tl;
-  const double W = L.w[a] * L.w[b];
-  const double feq = rho * W, gq = (cv - 1.0) * T, geq = gq * rho * W;
-  double fo = ft + om * (feq - ft), go = gt + om * (geq - gt);
+  const double om = 1.0 / tl, gq = (cv - 1.0) * T;
+  double Qxxx = 0.0, Qxxy = 0.0, Qxyy = 0.0, Qyyy = 0.0, qx = 0.0, qy = 0.0, dom = 0.0;
   if constexpr (QE) {
     // quasi-equilibria in the co-moving frame (v - u = sqrt(T) c):
     // Qbar = T^{3/2} sum c c c (f - f^eq), qbar = T^{1/2} sum c (g - g^eq)
-    const double om2 = 1.0 / (0.5 + (tl - 0.5) * tab->qe_ratio);
-    const double cx = xn[a], cy = xn[b];
-    const double nf = act ? ft - feq : 0.0, ng = act && TH ? gt - geq : 0.0;
-    const double Qxxx = group_sum<GS>(cx * cx * cx * nf), Qxxy = group_sum<GS>(cx * cx * cy * nf);
-    const double Qxyy = group_sum<GS>(cx * cy * cy * nf), Qyyy = group_sum<GS>(cy * cy * cy * nf);
-    const double qx = group_sum<GS>(cx * ng), qy = group_sum<GS>(cy * ng);
-    // f* - f^eq = W T^{-3/2}/6 Qbar : He3(c), Qbar = T^{3/2} (sums above)
-    const double h = Qxxx * (cx * cx * cx - 3.0 * cx) + 3.0 * Qxxy * (cx * cx * cy - cy) +
-                     3.0 * Qxyy * (cx * cy * cy - cx) + Qyyy * (cy * cy * cy - 3.0 * cy);
-    fo += (om - om2) * W * h / 6.0;
-    if (TH) go += (om - om2) * W * (qx * cx + qy * cy);
-  }
-  if (act) {
-    fout[(long long)i * pa.ncell + k] = fo;
-    if (TH) fout[(long long)(Q + i) * pa.ncell + k] = go;
-    if (li == 0) {
-      frout[k] = ux;
-      frout[pa.ncell + k] = uy;
-      frout[2 * pa.ncell + k] = 0.0;
-      frout[3 * pa.ncell + k] = T;
-      atomicAdd(itsum, (unsigned long long)it);
-      atomicMax(itmax, it);
+    dom = om - 1.0 / (0.5 + (tl - 0.5) * tab->qe_ratio);
+#pragma unroll
+    for (int b = 0; b < N; ++b) {
+      const double cx = xa, cy = xn[b], feq = rho * (wa * L.w[b]);
+      const double nf = own_f ? ft[b] - feq : 0.0, ng = own_f && TH ? gt[TH ? b : 0] - gq * feq : 0.0;
+      Qxxx += cx * cx * cx * nf;
+      Qxxy += cx * cx * cy * nf;
+      Qxyy += cx * cy * cy * nf;
+      Qyyy += cy * cy * cy * nf;
+      qx += cx * ng;
+      qy += cy * ng;
     }
+    Qxxx = cell_sum<CW>(Qxxx);
+    Qxxy = cell_sum<CW>(Qxxy);
+    Qxyy = cell_sum<CW>(Qxyy);
+    Qyyy = cell_sum<CW>(Qyyy);
+    qx = cell_sum<CW>(qx);
+    qy = cell_sum<CW>(qy);
+  }
+#pragma unroll
+  for (int b = 0; b < N; ++b) {
+    const double W = wa * L.w[b], feq = rho * W;
+    double fo = ft[b] + om * (feq - ft[b]), go = 0.0;
+    if (TH) go = gt[TH ? b : 0] + om * (gq * feq - gt[TH ? b : 0]);
+    if constexpr (QE) {
+      // f* - f^eq = W T^{-3/2}/6 Qbar : He3(c), Qbar = T^{3/2} (sums above)
+      const double cx = xa, cy = xn[b];
+      const double h = Qxxx * (cx * cx * cx - 3.0 * cx) + 3.0 * Qxxy * (cx * cx * cy - cy) +
+                       3.0 * Qxyy * (cx * cy * cy - cx) + Qyyy * (cy * cy * cy - 3.0 * cy);
+      fo += dom * W * h / 6.0;
+      if (TH) go += dom * W * (qx * cx + qy * cy);
+    }
+    if (own_f) {
+      fout[(long long)(a + N * b) * pa.ncell + k] = fo;
+      if (TH) fout[(long long)(Q + a + N * b) * pa.ncell + k] = go;
+    }
+  }
+  if (cell_ok && li == 0) {
+    frout[k] = ux;
+    frout[pa.ncell + k] = uy;
+    frout[2 * pa.ncell + k] = 0.0;
+    frout[3 * pa.ncell + k] = T;
+  }
+  // passes of the workgroup's cells, added to its own slot of the statistics
+  // (launches that share a slot follow one another on the stream).  Atomics of
+  // every wave on one counter took 385 us of a 432 us launch (512^2): updates of
+  // one address are served one after the other, at about 12 ns each.
+  int ws = cell_ok && li == 0 ? it : 0, wm = ws;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    ws += __shfl_xor(ws, o);
+    wm = max(wm, __shfl_xor(wm, o));
+  }
+  if (lane == 0) {
+    wstat[w][0] = ws;
+    wstat[w][1] = wm;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    unsigned long long *st = stats + 2 * ((size_t)blockIdx.y * gridDim.x + blockIdx.x);
+    unsigned long long m = st[1];
+    int sum = 0;
+#pragma unroll
+    for (int v = 0; v < Tr::TY; ++v) {
+      sum += wstat[v][0];
+      m = m > (unsigned)wstat[v][1] ? m : (unsigned)wstat[v][1];
+    }
+    st[0] += sum;
+    st[1] = m;
+  }
+}
+
+// pass counts of every workgroup: out[0] their sum, out[1] the maximum
+__global__ void __launch_bounds__(256)
+k_pond_stats(const unsigned long long *__restrict__ slots, long long n, unsigned long long *__restrict__ out) {
+  __shared__ unsigned long long ss[256], sx[256];
+  unsigned long long s = 0, m = 0;
+  for (long long t = threadIdx.x; t < n; t += 256) {
+    s += slots[2 * t];
+    m = max(m, slots[2 * t + 1]);
+  }
+  ss[threadIdx.x] = s;
+  sx[threadIdx.x] = m;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) {
+      ss[threadIdx.x] += ss[threadIdx.x + w];
+      sx[threadIdx.x] = max(sx[threadIdx.x], sx[threadIdx.x + w]);
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    out[0] = ss[0];
+    out[1] = sx[0];
   }
 }
 
@@ -691,26 +933,39 @@ int msl_pond_launch_set_mask(msl_ctx *c, const uint8_t *mask, int conv) {
   return rc;
 }
 
-template <int N, bool TH, bool QE>
+template <int N, bool TH, bool QE, bool SPX>
 static int pond_step_n(msl_ctx *c, int lat) {
-  constexpr int TW = PondTraits<N, TH>::TW;
+  using Tr = PondTraits<N, TH, SPX>;
   const PondArgs pa = pond_args(c);
-  const dim3 grid((unsigned)((pa.nx + TW - 1) / TW), (unsigned)pa.ny);
-  hipLaunchKernelGGL((k_pond_step<N, TH, QE>), grid, dim3(256), 0, c->stream, c->dtab, lat, c->cls, pa,
+  const dim3 grid((unsigned)((pa.nx + Tr::CW - 1) / Tr::CW), (unsigned)((pa.ny + Tr::TY - 1) / Tr::TY));
+  hipLaunchKernelGGL((k_pond_step<N, TH, QE, SPX>), grid, dim3(256), 0, c->stream, c->dtab, lat, c->cls, pa,
                      c->pond_f[lat][c->cur], c->pond_fr[c->cur], c->pond_f[lat][c->cur ^ 1],
-                     c->pond_fr[c->cur ^ 1], c->flag, c->pond_stats, (int *)(c->pond_stats + 1), c->pond_wall);
+                     c->pond_fr[c->cur ^ 1], c->flag, c->pond_slots, c->pond_wall);
   return hipGetLastError() == hipSuccess ? MSL_OK : MSL_EHIP;
 }
 
 template <bool TH, bool QE>
 static int pond_step_th(msl_ctx *c, int lat) {
+  // Point columns on lanes of their own: N = 5 always (the two-set shock's
+  // D2Q25 launch 94 us without, 45 us with); N = 3, 4 while the plain layout's
+  // 64-cell workgroups leave three CUs in four idle (12 or 9 of 16 lanes work:
+  // thermal D2Q16 at 144 workgroups 36.6 us a step with, 35.1 without; at 650
+  // 89 against 61); N = 6 has no room for them in 16 lanes.
+  const long long wgs = (long long)((c->geo.nx + 15) / 16) * ((c->geo.ny + 3) / 4);
+  const bool spx = wgs <= 64;
   switch (c->htab.lat[lat].n) {
-    case 3: return pond_step_n<3, TH, QE>(c, lat);
-    case 4: return pond_step_n<4, TH, QE>(c, lat);
-    case 5: return pond_step_n<5, TH, QE>(c, lat);
-    case 6: return pond_step_n<6, TH, QE>(c, lat);
+    case 3: return spx ? pond_step_n<3, TH, QE, true>(c, lat) : pond_step_n<3, TH, QE, false>(c, lat);
+    case 4: return spx ? pond_step_n<4, TH, QE, true>(c, lat) : pond_step_n<4, TH, QE, false>(c, lat);
+    case 5: return pond_step_n<5, TH, QE, true>(c, lat);
+    case 6: return pond_step_n<6, TH, QE, false>(c, lat);
   }
   return MSL_EINVAL;
+}
+
+// the pass counts since the slots were cleared into pond_stats
+int msl_pond_launch_stats(msl_ctx *c) {
+  hipLaunchKernelGGL(k_pond_stats, dim3(1), dim3(256), 0, c->stream, c->pond_slots, c->pond_nslot, c->pond_stats);
+  return hipGetLastError() == hipSuccess ? MSL_OK : MSL_EHIP;
 }
 
 // one step: [the Knudsen-number criterion pass], one launch per set, the band
