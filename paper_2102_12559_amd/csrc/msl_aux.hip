@@ -938,15 +938,24 @@ int msl_launch_bc(msl_ctx *c, char *bl, char *bh) {
   if (copies(0) && !c->xg_ok)
     DISPATCH_STORE(c, k_bc_xcopy, dim3(nblocks((long long)2 * MSL_G * g.ny * nz), np0 + np1), blk, g, b,
                    bl, bh, np0);
+  // ghost rows and slabs of the sets that do not map them themselves
+  char *base[2] = {bl, bh};
+  int np[2] = {np0, np1}, nset = 0;
+  for (int l = 0; l < c->nlat; ++l)
+    if (!(c->walk_sets & (1 << l))) {
+      base[nset] = l ? bh : bl;
+      np[nset++] = l ? np1 : np0;
+    }
+  if (nset == 0) return last_err();
+  const int npl = np[0] + (nset > 1 ? np[1] : 0);
+  char *b1 = nset > 1 ? base[1] : nullptr;
   if (copies(1)) {
     const long long n = (long long)g.pitch * esz / 16 * 2 * MSL_G * nz;
-    hipLaunchKernelGGL(k_bc_blocks<1>, dim3(nblocks(n), np0 + np1), blk, 0, c->stream, g, b, bl, bh, np0,
-                       esz);
+    hipLaunchKernelGGL(k_bc_blocks<1>, dim3(nblocks(n), npl), blk, 0, c->stream, g, b, base[0], b1, np[0], esz);
   }
   if (copies(2)) {
     const long long n = (long long)g.rows * g.pitch * esz / 16 * 2 * MSL_G;
-    hipLaunchKernelGGL(k_bc_blocks<2>, dim3(nblocks(n), np0 + np1), blk, 0, c->stream, g, b, bl, bh, np0,
-                       esz);
+    hipLaunchKernelGGL(k_bc_blocks<2>, dim3(nblocks(n), npl), blk, 0, c->stream, g, b, base[0], b1, np[0], esz);
   }
   return last_err();
 }

@@ -583,6 +583,12 @@ int msl_create(const msl_config *cfg, void *ws, size_t bytes, void *stream, msl_
     }
     c->zgm = ok ? m : 0;
   }
+  if (cfg->dim == 3 && !cfg->thermal && cfg->store != MSL_FP64) {
+    for (int l = 0; l < c->nlat; ++l)
+      if (cfg->store != MSL_FP32 || c->htab.lat[l].n == 3) c->walk_sets |= 1 << l;
+    for (int f = 0; f < 6; ++f)
+      c->walk |= (cfg->bc[f] == MSL_BC_PERIODIC ? 1 : (cfg->bc[f] == MSL_BC_OUTFLOW_ZG ? 2 : 0)) << (2 * f);
+  }
   // step graphs: one block per criterion period (at most 64 steps), else 16
   c->gmode = 0;
   c->gB = cfg->crit_kind && cfg->crit_every > 0 && c->nlat > 1 && cfg->crit_every <= 64 ? cfg->crit_every : 16;

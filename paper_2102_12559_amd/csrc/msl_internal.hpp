@@ -166,6 +166,12 @@ struct msl_ctx {
   // the x ghost columns of the new buffer (xmir), so the next ghost fill
   // leaves out the x faces while xg_ok says they hold the current values
   int xmir, xg_ok;
+  // 3D sets that run a column walk (bit l: set l; athermal, 16-bit storage or
+  // FP32 D3Q27): the walk maps ghost rows and slabs by the faces' rules itself,
+  // only their ghost columns are filled; walk: two bits per face (1 periodic, 2
+  // zero-gradient, 0 stored ghosts: fixed, diffuse)
+  int walk_sets;
+  int walk;
   // live tiles of the high-order set, ascending (sparse stream-collide
   // launches walk this list instead of the whole tile grid); tl_ok: the list
   // matches the current tile flags

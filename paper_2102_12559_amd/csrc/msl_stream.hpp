@@ -329,6 +329,10 @@ static bool fusable_n(int D) {
   return D == 2 && SC2Traits<S, TH, N>::fits;
 }
 
+// 3D sets that run a column walk
+template <typename S, bool TH>
+constexpr bool msl_walk_set(int n) { return !TH && (sizeof(S) == 2 || (sizeof(S) == 4 && n == 3)); }
+
 template <typename S, bool TH, int N, int D, bool QE = false>
 static int launch_one(msl_ctx *c, int lat, const char *in, char *out, char *oth) {
   using Tr = SCTraits<S, TH, N, D>;
@@ -350,18 +354,23 @@ static int launch_one(msl_ctx *c, int lat, const char *in, char *out, char *oth)
                        (const S *)in, (S *)out, c->cls, c->tflag);
   } else {
     if (oth) return MSL_EINVAL;
-    if constexpr (SC3ZTraits<S, TH, N>::fits) {
-      // 3D: columns of 64 x 4 x ZC cells walked along z; the high-order set
-      // of a large grid runs over the compact list of its live columns
-      using T3 = SC3ZTraits<S, TH, N>;
-      {
-        const int ncz = (g.nz + T3::ZC - 1) / T3::ZC;
-        const long long tiles = (long long)g.ntx * g.nty * ncz;
-        const long long fit = 256LL * ((160 * 1024) / T3::LDS_BYTES);
-        if (lat != 0 && tiles > 4 * fit) {
+    if constexpr (msl_walk_set<S, TH>(N)) {
+      // 3D, athermal 16-bit storage and FP32 D3Q27: columns of 64 x 4 x zc cells
+      // walked along z; the high-order set of a large grid runs over the
+      // compact list of its live columns.
+      // Column length: a column loads two slabs more than it has cells, and the
+      // launch takes as long as its columns have steps.  8 cells (FP16 D3Q27
+      // and D3Q64, one stream: 200^3 396 + 371 us against 415 + 403 at 16; 256^3
+      // 644 + 635 against 631 + 643), 4 where 8 leave CUs idle (64^3 FP16: a step
+      // of 118 against 84 us)
+      const long long cols = (long long)g.ntx * g.nty;
+      const int zc = cols * ((g.nz + 7) / 8) >= 256 ? MSL_WALK_ZC : 4;
+      const int ncz = (g.nz + zc - 1) / zc;
+      auto walk = [&](auto dense, auto list, int nt) -> int {
+        if (lat != 0 && cols * ncz > MSL_WALK_LIST_MIN) {
           if (c->capturing) return MSL_ESTATE;   // the list length is read by the host
-        if (!c->tl_ok) {
-            if (msl_launch_tile_list(c, lat, 1, T3::ZC)) return MSL_EHIP;
+          if (!c->tl_ok) {
+            if (msl_launch_tile_list(c, lat, 1, zc)) return MSL_EHIP;
             int n = 0;
             if (hipMemcpyAsync(&n, c->tcount, sizeof(int), hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
                 hipStreamSynchronize(c->stream) != hipSuccess)
@@ -370,20 +379,21 @@ static int launch_one(msl_ctx *c, int lat, const char *in, char *out, char *oth)
             c->tl_ok = 1;
           }
           if (c->tl_n == 0) return MSL_OK;
-          hipLaunchKernelGGL((k_sc3d_zm<S, TH, N, true>), dim3((unsigned)c->tl_n), dim3(T3::NT), 0, c->stream,
-                             c->dtab, lat, g, (const S *)in, (S *)out, c->cls, c->tflag, 0, c->xmir,
-                             c->tlist, c->tcount);
-          return hipGetLastError() == hipSuccess ? MSL_OK : MSL_EHIP;
+          hipLaunchKernelGGL(list, dim3((unsigned)c->tl_n), dim3(nt), 0, c->stream, c->dtab, lat, g, (const S *)in,
+                             (S *)out, c->cls, c->tflag, 0, c->xmir, c->walk, zc, c->tlist, c->tcount);
+        } else {
+          dim3 grid((g.nx + MSL_TX - 1) / MSL_TX, (g.ny + MSL_MTY - 1) / MSL_MTY, ncz);
+          hipLaunchKernelGGL(dense, grid, dim3(nt), 0, c->stream, c->dtab, lat, g, (const S *)in, (S *)out, c->cls,
+                             c->tflag, lat == 0, c->xmir, c->walk, zc, (const int *)nullptr, (const int *)nullptr);
         }
-        dim3 grid((g.nx + MSL_TX - 1) / MSL_TX, (g.ny + MSL_MTY - 1) / MSL_MTY, ncz);
-        hipLaunchKernelGGL((k_sc3d_zm<S, TH, N>), grid, dim3(T3::NT), 0, c->stream, c->dtab, lat, g,
-                           (const S *)in, (S *)out, c->cls, c->tflag, lat == 0, c->xmir, nullptr, nullptr);
         return hipGetLastError() == hipSuccess ? MSL_OK : MSL_EHIP;
-      }
-    }
-    // 3D sets whose planes do not fit the walk's register budget: planes
-    // streamed through LDS in chunks; the high-order set of a large grid runs
-    // over the compact list of its live tiles (as in 2D)
+      };
+      if constexpr (sizeof(S) == 2) return walk(k_sc3d_zr<S, N, false>, k_sc3d_zr<S, N, true>, SC3RTraits<S, N>::NT);
+      else return walk(k_sc3d_zm<false>, k_sc3d_zm<true>, SC3ZTraits::NT);
+    } else {
+    // the other 3D sets (FP64, thermal, FP32 D3Q64): planes streamed through LDS
+    // in chunks; the high-order set of a large grid runs over the compact list of
+    // its live tiles (as in 2D)
     using T3 = SC3Traits<S, TH, N>;
     const long long tiles = (long long)g.ntx * g.nty * ((g.ntz + T3::RZ - 1) / T3::RZ);
     const long long fit = 256LL * ((160 * 1024) / T3::LDS_BYTES);
@@ -409,6 +419,7 @@ static int launch_one(msl_ctx *c, int lat, const char *in, char *out, char *oth)
     dim3 grid((g.nx + MSL_TX - 1) / MSL_TX, (g.ny + MSL_MTY - 1) / MSL_MTY, (g.nz + T3::RZ - 1) / T3::RZ);
     hipLaunchKernelGGL((k_sc3d_res<S, TH, N>), grid, block, 0, c->stream, c->dtab, lat, g,
                        (const S *)in, (S *)out, c->cls, c->tflag, lat == 0, c->xmir, nullptr, nullptr);
+    }
   }
   return hipGetLastError() == hipSuccess ? MSL_OK : MSL_EHIP;
 }

@@ -1,29 +1,37 @@
-// msl_stream3z.hpp -- the 3D stream-and-collide kernel that marches along z.
+// msl_stream3z.hpp -- the 3D stream-and-collide kernels that march along z, for
+// athermal sets: D3Q27 in FP32 storage (first), D3Q27 and D3Q64 in 16-bit
+// storage (below).  FP64, thermal and FP32 D3Q64 runs use the chunked kernel of
+// msl_stream3.hpp.
 //
-// A workgroup owns a column of 64 x 4 x ZC cells (one y row per wave, one x
-// cell per lane; 16-bit D3Q64: four waves per row, each with the planes of
-// one z node) and walks it from its lowest z cell upwards.  At each step
-// of the walk it brings one z slab of every plane's departure window into
-// LDS (direct-to-LDS buffer loads of 6 rows x 66 cells: the departure offset
-// x - v_i dt is the same for every cell of a plane, so the slab is the
-// column's cross-section shifted by the plane's base offset), interpolates
-// the slab along x and y (eq. reconstructionPond, 3-point Lagrange weights),
+// A workgroup owns a column of 64 x 4 x zc cells and walks it from its lowest
+// z cell upwards.  Its nine waves share out the populations: a wave holds the
+// three planes of one z and one y node for all four rows of the column, one x
+// cell per lane.  At each step of the walk a wave brings one z
+// slab of each of its planes' departure windows into LDS (direct-to-LDS
+// buffer loads of 6 rows x 66 cells: the departure offset x - v_i dt is the
+// same for every cell of a plane, so the slab is the column's cross-section
+// shifted by the plane's base offset), interpolates the slab along x (six
+// rows) and y (four cells; eq. reconstructionPond, 3-point Lagrange weights),
 // and combines it with the two slabs before it, which each lane keeps in
-// registers, into the population streamed to its cell (the z interpolation).
-// Every slab of a column's window is read once per column instead of once
-// per group of z cells, and each lane reconstructs one new slab per
-// population and step instead of all three.  The cell then collides in
-// registers: moments, FP64 equilibrium factors in the run's frame, BGK
-// relaxation (eqs. Pond_f/g, feqL, geqL) and buffer stores whose
-// out-of-range offset drops the writes of foreign or outside cells.  The
-// loads of the next slab are issued before the collision, so they are in
-// flight while it runs.
+// registers, into the populations streamed to its cells (the z interpolation).
+// Every slab of a column's window is read once per column.  No wave reads
+// another's slabs, so the loads need no barrier, only the wave's own wait;
+// the loads of the next slab are in flight while the cells collide.
 //
-// Each lane holds three values per population (two partial sums or slabs and
-// the streamed value), so the kernel serves the velocity sets whose planes fit
-// the register file: athermal D3Q27 in 16-bit and FP32 storage (three waves
-// per SIMD) and athermal D3Q64 in 16-bit storage (one wave per SIMD).  The
-// others use the chunked kernel of msl_stream3.hpp.
+// The cells collide in registers: the waves exchange their partial moments
+// through LDS; one wave per row adds them in wave order and evaluates the
+// FP64 equilibrium factors in the run's frame; every wave relaxes its own
+// populations (BGK, eqs. Pond_f/g, feqL, geqL) and stores them with buffer
+// stores whose out-of-range offset drops the writes of foreign or outside
+// cells.  Two barriers per step.
+//
+// What bounds it: on large grids the stores (a step's burst of R PW stores per
+// wave is issued at 16 to 30 cycles each), VALU issue at about a third; on small
+// grids the chain of a step's phases.  The form before (one wave per row with
+// every plane of its cells, columns of 32) interpolated each row three times
+// and read nine LDS values per population and cell; six rows shared by four
+// cells take 4.5 reads, and the factors are formed once per cell.
+// 150 x 130 x 141: 367 us before, 267 us now; 64^3: 240 us before, 24 us now.
 #pragma once
 #include <utility>
 
@@ -40,14 +48,28 @@ __device__ __forceinline__ void msl_wait_vm() {
   asm volatile("" ::: "memory");
 }
 
-// workgroup barrier for LDS traffic only: this wave's LDS reads have returned
-// (lgkmcnt 0) and no memory operation moves across it; unlike
-// __syncthreads() it does not wait for outstanding global stores
-__device__ __forceinline__ void msl_lds_barrier() {
+// this wave's LDS operations have completed (lgkmcnt 0), and no memory
+// operation moves across
+__device__ __forceinline__ void msl_wait_lds() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
+  asm volatile("" ::: "memory");
+}
+
+// workgroup barrier for LDS traffic only; unlike __syncthreads() it does not
+// wait for outstanding global stores
+__device__ __forceinline__ void msl_lds_barrier() {
+  msl_wait_lds();
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
+}
+
+// 1 / v to FP64 rounding (v normal and finite): the hardware's estimate and two
+// Newton steps, a shorter dependent chain than the IEEE division
+__device__ __forceinline__ double msl_rcp(double v) {
+  double r = __builtin_amdgcn_rcp(v);
+  r = __builtin_fma(__builtin_fma(-v, r, 1.0), r, r);
+  return __builtin_fma(__builtin_fma(-v, r, 1.0), r, r);
 }
 
 // a 16-bit stored element (the low 16 bits of u) as float
@@ -62,73 +84,46 @@ __device__ __forceinline__ float half_elem<bf16_t>(uint32_t u) { return __uint_a
 template <typename S>
 __device__ __forceinline__ float half_elem(uint32_t) { return 0.0f; }
 
-template <typename S, bool TH, int N>
+// columns of the high-order set beyond which its launch runs over the list of
+// live columns: 32 per CU, of which a criterion's set fills a part
+#define MSL_WALK_LIST_MIN 8192
+#define MSL_WALK_ZC 8   // most cells of a column along z (bits of a 32-bit word per lane)
+
 struct SC3ZTraits {
-  using T = StoreTraits<S>;
-  using C = typename T::C;
-  static constexpr int Q = N * N * N;
-  static constexpr int NP = TH ? 2 * Q : Q;
-  static constexpr int SZ = (int)sizeof(S);
-  static constexpr int LWD = (66 * SZ + 3) / 4 + (SZ < 4 ? 1 : 0);   // dwords per window row
-  static constexpr int SD = 6 * LWD;                                  // dwords of a plane's slab
-  static constexpr int M = (SD + 255) / 256;                          // DMA instructions per wave
-  // LDS dwords per plane: 16-bit slabs (204 dwords) are padded to the 256
-  // that one DMA instruction of the four waves writes, so that every lane
-  // loads (no exec-mask branch per plane and step); FP32 slabs (396 dwords)
-  // keep their size, the padding would cost a wave per SIMD of LDS occupancy
-  static constexpr bool PAD = SZ == 2;
-  static constexpr int SDP = PAD ? M * 256 : SD;
-  static constexpr int ZC = 32;                                       // cells per column along z
-  static_assert(ZC <= 32, "the lane's cells of a column are kept as bits of a 32-bit word");
-  // planes per LDS chunk: every plane of a step in one chunk where 64 KB hold them
-  static constexpr int BUDGET = 64 * 1024;
-  static constexpr int CHMAX = BUDGET / (SDP * 4) < 1 ? 1 : BUDGET / (SDP * 4);
-  static constexpr int NCH = (NP + CHMAX - 1) / CHMAX;
-  static constexpr int CH = (NP + NCH - 1) / NCH;
-  static constexpr int LDS_BYTES = CH * SDP * 4;
-  static constexpr int REGW = SZ == 8 ? 2 : 1;
-  // 16-bit D3Q64: four waves per row of cells, each holding the 16 planes of
-  // one z node (the parts differ by a plane offset and a z-node offset;
-  // partial moments summed through LDS), so that four waves per SIMD fit the
-  // register file instead of one
-  static constexpr bool SPLIT = !TH && N == 4 && SZ == 2;
-  static constexpr int NHW = SPLIT ? 4 : 1;   // waves per row of cells
-  static constexpr int NT = 256 * NHW;        // threads per workgroup
-  static constexpr int NPW = NP / NHW;        // planes per wave
-  // registers per lane: three per plane and about 50 besides (D3Q27: 167
-  // VGPRs, three waves per SIMD); D3Q64 with all planes in one wave needs
-  // about 300, VGPRs and AGPRs together
-  static constexpr int VREG = 3 * NPW * REGW + (N == 3 ? 48 : 110);
-  // athermal D3Q27 in 16-bit and FP32 storage, athermal D3Q64 in 16-bit
-  // storage (at one wave per SIMD: 3355 against 3541 us for the chunked
-  // kernel on a 256^3 grid, while FP32 D3Q64 ran slower, 4941 against 4245
-  // us); FP64 values and the g planes of the thermal model would spill
-  static constexpr bool fits = !TH && (N == 3 ? SZ <= 4 : (N == 4 && SZ == 2));
-  static constexpr int WG_LDS = (160 * 1024) / LDS_BYTES;
-  static constexpr int W_REG = 512 / VREG;
-  // waves per SIMD: NHW per resident workgroup
-  static constexpr int WAVES0 = WG_LDS * NHW < W_REG ? WG_LDS * NHW : W_REG;
-  static constexpr int WAVES1 = WAVES0 / NHW * NHW < NHW ? NHW : WAVES0 / NHW * NHW;
-  static constexpr int WAVES = WAVES1 > 8 ? 8 : WAVES1;
+  static constexpr int N = 3, Q = N * N * N;
+  // one z and one y node per wave (all three y nodes, in three waves of 178
+  // registers, measured 82 against 54 us on 64^3 and 644 against 598 us on 200^3)
+  static constexpr int NWV = N * N;            // waves per workgroup
+  static constexpr int NT = 64 * NWV;
+  static constexpr int PW = N;                 // planes of a wave
+  static constexpr int R = MSL_MTY;            // rows
+  // a window row is loaded in 16-byte chunks
+  static constexpr int CPR = (66 * 4 + 15) / 16;
+  static constexpr int ROWB = 16 * CPR;
+  static constexpr int CPP = (R + 2) * CPR;    // chunks of a plane's slab
+  static constexpr int M = (CPP + 63) / 64;    // DMA instructions per plane
+  static constexpr int SLAB = 16 * CPP;
+  static constexpr int NPS = 2;                // partial sums of a wave: rho, j_x
+  static constexpr int NFAC = 3 * N + 1;       // equilibrium factors, omega
+  static constexpr int LDS_BYTES = Q * SLAB + ((NWV - 1) * NPS + NFAC) * 256 * 4;
+  // waves per SIMD that the registers have to allow (two workgroups of nine
+  // waves take five on some SIMD)
+  static constexpr int WAVES = 5;
 };
 
-template <typename S, bool TH, int N, bool LIST = false>
-__global__ void __launch_bounds__((SC3ZTraits<S, TH, N>::NT))
-    __attribute__((amdgpu_waves_per_eu(SC3ZTraits<S, TH, N>::WAVES)))
-k_sc3d_zm(const Tab *__restrict__ tab, int lat, Geo g, const S *__restrict__ in,
-          S *__restrict__ out, const uint8_t *__restrict__ cls,
-          const uint8_t *__restrict__ tflag, int remap, int xmir, const int *__restrict__ tlist,
+template <bool LIST>
+__global__ void __launch_bounds__(SC3ZTraits::NT) __attribute__((amdgpu_waves_per_eu(SC3ZTraits::WAVES)))
+k_sc3d_zm(const Tab *__restrict__ tab, int lat, Geo g, const float *__restrict__ in,
+          float *__restrict__ out, const uint8_t *__restrict__ cls,
+          const uint8_t *__restrict__ tflag, int remap, int xmir, int faces, int zc, const int *__restrict__ tlist,
           const int *__restrict__ tcount) {
-  using Tr = SC3ZTraits<S, TH, N>;
-  using T = typename Tr::T;
-  using C = typename Tr::C;
-  constexpr int Q = Tr::Q, NP = Tr::NP, SD = Tr::SD, SDP = Tr::SDP, M = Tr::M, CH = Tr::CH, NCH = Tr::NCH;
-  constexpr int LWD = Tr::LWD, SZ = Tr::SZ, ZC = Tr::ZC;
-  constexpr bool SPL = Tr::SPLIT;
-  constexpr int NPW = Tr::NPW;
-  static_assert(!SPL || (NCH == 1 && NP == Q), "the split walk: one chunk, f planes only");
-  __shared__ uint32_t sm[CH * SDP];
-  __shared__ float smom[SPL ? Tr::NHW : 1][SPL ? 4 : 1][SPL ? 256 : 1];   // partial moments per part
+  using Tr = SC3ZTraits;
+  typedef float C;
+  constexpr int N = Tr::N, Q = Tr::Q, NWV = Tr::NWV, PW = Tr::PW, R = Tr::R, M = Tr::M;
+  constexpr int SZ = 4, ROWB = Tr::ROWB, CPR = Tr::CPR, CPP = Tr::CPP, SLAB = Tr::SLAB, NPS = Tr::NPS;
+  __shared__ __align__(16) char sm[Q * SLAB];
+  __shared__ float s_part[(NWV - 1) * NPS][256];   // partial moments of the waves that do not own the row
+  __shared__ float s_fac[Tr::NFAC][256];           // equilibrium factors per axis (x with rho), omega
   const LatTab &L = tab->lat[lat];
   // the column: from the grid (XCD-aware order for dense launches), or one
   // workgroup per entry of the compact list of live columns (sparse launches)
@@ -142,183 +137,176 @@ k_sc3d_zm(const Tab *__restrict__ tab, int lat, Geo g, const S *__restrict__ in,
     tile = remap ? msl_xcd_tile(lin, (int)(gridDim.x * gridDim.y * gridDim.z)) : lin;
   }
   const int bx = tile % g.ntx, by = (tile / g.ntx) % g.nty;
-  const int z0 = tile / (g.ntx * g.nty) * ZC;
+  const int z0 = tile / (g.ntx * g.nty) * zc;
   const int x0 = bx * MSL_TX, y0 = by * MSL_MTY;
-  const int zn = g.nz - z0 < ZC ? g.nz - z0 : ZC;   // cells of the column (>= 1)
+  const int zn = g.nz - z0 < zc ? g.nz - z0 : zc;   // cells of the column (>= 1)
   {
     uint8_t any = 0;
     for (int k = 0; k < zn; ++k) any |= tflag[((long long)(z0 + k) * g.nty + by) * g.ntx + bx];
     if (!(any & (1 << lat))) return;
   }
-  // (the wave index as a scalar: the LDS destinations of the DMA are formed
-  // in scalar registers)
-  // w: the wave's row of cells; hf: its half of the planes (split walk), which
-  // starts at plane kb and z node ccb
+  // the wave's z node cc, y node b0 and first plane kb, as scalars
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int w = wv & 3, hf = SPL ? wv >> 2 : 0;
-  const int kb = hf * NPW, ccb = kb / (N * N);
+  const int cc = wv / N, b0 = wv % N, kb = wv * N;
   const unsigned pitch_b = (unsigned)g.pitch * SZ;
   const unsigned plane_b = (unsigned)g.plane * SZ;
   const unsigned slab_b = (unsigned)g.rows * pitch_b;
-  // plane-independent byte offsets of this lane's slab dwords; lanes past the
-  // slab's SD dwords issue no load
+  // the cells of this velocity set along the column, as bits per cell (bit k:
+  // z0 + k): 8 z cells per thread, through LDS
+  uint32_t mine[R];
+  {
+    uint8_t *bits = (uint8_t *)s_fac;
+    for (int e = threadIdx.x; e < 1024; e += Tr::NT) {
+      const int q = e >> 8, ci = e & 255, x = x0 + (ci & 63), y = y0 + (ci >> 6);
+      unsigned m = 0;
+      if (x < g.nx && y < g.ny)
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if (8 * q + j < zn)
+            m |= (unsigned)((cls[((long long)(z0 + 8 * q + j) * g.ny + y) * g.nx + x] & 1) == lat) << j;
+      bits[4 * ci + q] = (uint8_t)m;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) mine[r] = ((const uint32_t *)bits)[64 * r + lane];
+  }
+  // interpolation weights and window offsets of the departure stencil
+  C wx[3][N], wy[3], wz[3];
+  int offx[N];
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+#pragma unroll
+    for (int a = 0; a < N; ++a) wx[s][a] = L.af[0][a][s];
+    wy[s] = L.af[1][b0][s];
+    wz[s] = L.af[2][cc][s];
+  }
+#pragma unroll
+  for (int a = 0; a < N; ++a) offx[a] = L.n0[0][a] - 1;
+  // Ghost rows and slabs.  A y or z coordinate of the window outside the domain
+  // is mapped by its face's rule (two bits of `faces` per face: 1 periodic,
+  // wrapped; 2 zero-gradient, clamped; 0 fixed or diffuse, the stored ghost
+  // layer) when the slab is loaded, rows by the lanes' addresses and slabs by
+  // the scalar offset, so no pass copies those ghost layers (41 to 46 us a step
+  // at 150 x 130 x 141 FP32 and 256^3 FP16).  Ghost columns are stored: written as
+  // images below, or by the ghost fill.  (Loading them per plane into the
+  // staged rows, 24 lanes a plane, cost more than the images: the D3Q64 launch
+  // of the 256^3 run 505 against 475 us.)
+  auto mapped = [&](int ax, int p, int n) {
+    if (p >= 0 && p < n) return p;
+    const int rule = (faces >> (4 * ax + (p < 0 ? 0 : 2))) & 3;
+    return rule == 1 ? (p < 0 ? p + n : p - n) : (rule == 2 ? (p < 0 ? 0 : n - 1) : p);
+  };
+  // byte offsets inside a slab of this lane's chunks; lanes past the slab's CPP
+  // chunks issue no load
   unsigned voff[M];
-  bool vld[M];
 #pragma unroll
   for (int m = 0; m < M; ++m) {
-    const int d = lane + 64 * (w + 4 * m);
-    vld[m] = Tr::PAD || d < SD;   // padded: lanes past the slab load a valid dword into the pad
-    const int dd = d < SD ? d : SD - 1;
-    const int row = dd / LWD, col = dd - row * LWD;
-    voff[m] = (unsigned)row * pitch_b + (unsigned)col * 4u;
+    const int d = lane + 64 * m, row = d / CPR;
+    voff[m] = (unsigned)(mapped(1, y0 + L.n0[1][b0] - 1 + row, g.ny) + MSL_G) * pitch_b +
+              (unsigned)(d - row * CPR) * 16u;
   }
-  // per-node tables of each axis: interpolation weights and the window offset
-  // of the departure stencil (the z offset selects the first slab)
-  C wlo[3][N], wmid[3][N], whi[3][N];
-  int offx[N], offy[N], offz[N];
-#pragma unroll
-  for (int a = 0; a < N; ++a) {
-#pragma unroll
-    for (int ax = 0; ax < 3; ++ax) {
-      wlo[ax][a] = tsel<C>(L.a[ax][a][0], L.af[ax][a][0]);
-      wmid[ax][a] = tsel<C>(L.a[ax][a][1], L.af[ax][a][1]);
-      whi[ax][a] = tsel<C>(L.a[ax][a][2], L.af[ax][a][2]);
-    }
-    offx[a] = L.n0[0][a] - 1;
-    offy[a] = (L.n0[1][a] - 1) * g.pitch;
-    offz[a] = (L.n0[2][a] - 1) * g.rows * g.pitch;
-  }
-  // z tables from the wave's first z node on (split walk; ccb = 0 otherwise)
-  if constexpr (SPL) {
-#pragma unroll
-    for (int a = 0; a < N; ++a) {
-      const int az = a + ccb < N ? a + ccb : N - 1;
-      wlo[2][a] = tsel<C>(L.a[2][az][0], L.af[2][az][0]);
-      wmid[2][a] = tsel<C>(L.a[2][az][1], L.af[2][az][1]);
-      whi[2][a] = tsel<C>(L.a[2][az][2], L.af[2][az][2]);
-      offz[a] = (L.n0[2][az] - 1) * g.rows * g.pitch;
-    }
-  }
-  // byte offset of the column's first slab window (before the plane's shift)
-  const unsigned org0b = (unsigned)g.idx(x0, y0, z0) * SZ;
-  // DMA of step t's slab of planes [K0, K1) into LDS: slab z0 + n0_z - 1 + t.
+  const unsigned row0b = (unsigned)(g.xo + x0) * SZ;   // byte of x0 in a row
+  const int zw = z0 + L.n0[2][cc] - 1;                 // z of step 0's slab
+  // DMA of step t's slab of the wave's planes into LDS: slab z0 + n0_z - 1 + t.
   // Each plane has its own buffer descriptor (the range of one plane); the
   // base offsets pass through an empty asm at every call, so the per-plane
   // descriptors and offsets are formed here rather than hoisted out of the
   // walk (4 + 1 scalar registers per plane)
   const long long plane_b64 = g.plane * SZ;
-  auto issue = [&]<int K0, int K1>(const int t) {
-    unsigned ob = org0b + (unsigned)t * slab_b;
-    const char *pp = (const char *)in + (kb + K0) * plane_b64;
+  auto issue = [&](const int t) {
+    const int zm = mapped(2, zw + t, g.nz);
+    unsigned ob = (unsigned)(zm + MSL_G) * slab_b;
+    const char *pp = (const char *)in + kb * plane_b64;
     asm volatile("" : "+s"(ob), "+s"(pp));
-    msl_for_range<K0, K1>([&]<int K>() {
-      constexpr int i = K % Q, a = i % N, b = (i / N) % N, cc = i / (N * N);
-      const unsigned so = (ob + (unsigned)(offx[a] + offy[b] + offz[cc]) * SZ) & ~3u;
+    msl_for_planes<PW>([&]<int K>() {
+      const unsigned so = ob + row0b + (unsigned)(offx[K] * SZ);
       const __amdgpu_buffer_rsrc_t rs =
           __builtin_amdgcn_make_buffer_rsrc((void *)pp, (short)0, (int)plane_b, MSL_RSRC_WORD3);
 #pragma unroll
       for (int m = 0; m < M; ++m)
-        if (vld[m])
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(
-              rs, (msl_lds_t *)(sm + (SPL ? kb + K : K - K0) * SDP + 64 * (w + 4 * m)), 4, (int)voff[m], (int)so, 0, 0);
+        if ((m + 1) * 64 <= CPP || lane + 64 * m < CPP)
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (msl_lds_t *)(sm + (kb + K) * SLAB + 1024 * m), 16,
+                                                   (int)voff[m], (int)so, 0, 0);
       pp += plane_b64;
     });
   };
-  // LDS byte offset of the lane's first element in its wave's first window
-  // row.  Rows start 64-byte aligned in HBM (the pitch is a multiple of 64
-  // bytes and the column's x0 a multiple of 64 cells), so a plane's window
-  // starts at byte (offx SZ) mod 4 of its first dword: 0 or 2 for 16-bit
-  // storage, 0 otherwise.  The 16-bit elements are read one by one with
-  // 16-bit LDS reads (volatile, so that the compiler does not merge two of
-  // them into a 4-byte read at a 2-byte boundary, which stalls the LDS pipeline)
-  unsigned rb[N];
+  // LDS byte offset of the lane's first element in the first window row of the
+  // wave's first plane
+  unsigned rb = (unsigned)(kb * SLAB + lane * SZ);
+  // per plane and row: the x, y interpolated values of the two slabs before the
+  // new one (ha: slab t - 2, hb: slab t - 1) and the streamed value
+  C ha[PW][R], hb[PW][R], ftk[PW][R];
 #pragma unroll
-  for (int a = 0; a < N; ++a)
-    rb[a] = (unsigned)(w * LWD * 4 + lane * SZ) + (SZ == 2 ? (unsigned)(offx[a] & 1) * 2u : 0u);
-  // per plane: the two slabs before the new one (FP32 / FP64: x, y
-  // interpolated values ha = slab t - 2, hb = slab t - 1), or (16-bit storage)
-  // the z interpolation's partial sums of the next two cells
-  // (ha = w0 h_{t-2} + w1 h_{t-1}, hb = w0 h_{t-1}), which need no register moves
-  // as the walk advances; ftk: the streamed value
-  C ha[NPW], hb[NPW], ftk[NPW];   // (the wave's planes: all, or its half)
+  for (int k = 0; k < PW; ++k)
 #pragma unroll
-  for (int k = 0; k < NPW; ++k) ha[k] = hb[k] = C(0);
-  // the new slab of plane K: x then y interpolation, then the z interpolation
-  // of the three slabs into the streamed value of cell z0 + t - 2
-  auto recon = [&]<int K>() {
-    constexpr int i = K % Q, a = i % N, b = (i / N) % N, cc = i / (N * N);
-    const char *base = (const char *)sm + ((SPL ? kb : 0) + K % CH) * SDP * 4 + rb[a];
-    const C wx0 = wlo[0][a], wx2 = whi[0][a], wy0 = wlo[1][b], wy2 = whi[1][b], wz0 = wlo[2][cc],
-            wz2 = whi[2][cc];
-    C hy[3];
+    for (int r = 0; r < R; ++r) ha[k][r] = hb[k][r] = C(0);
+  // the lane's window values of three rows of plane K (H: the lower or upper
+  // three): three of each row
+  static_assert(R == 4, "a slab's six rows are read three at a time");
+  auto fetch = [&]<int K, int H>(C (&v)[3][3]) {
+    typedef volatile const __attribute__((address_space(3))) float lds_f32;
+    const char *base = (const char *)sm + rb + K * SLAB + 3 * H * ROWB;
 #pragma unroll
-    for (int dy = 0; dy < 3; ++dy) {
-      const char *row = base + dy * LWD * 4;
-      C v0, v1, v2;
-      if constexpr (SZ == 8) {
-        v0 = (C)lds_elem_d<S>(row); v1 = (C)lds_elem_d<S>(row + 8); v2 = (C)lds_elem_d<S>(row + 16);
-      } else if constexpr (SZ == 4) {
-        v0 = (C)lds_elem<S>(row); v1 = (C)lds_elem<S>(row + SZ); v2 = (C)lds_elem<S>(row + 2 * SZ);
-      } else {
-        typedef volatile const __attribute__((address_space(3))) uint16_t lds_u16;
-        v0 = (C)half_elem<S>(*(lds_u16 *)row);
-        v1 = (C)half_elem<S>(*(lds_u16 *)(row + 2));
-        v2 = (C)half_elem<S>(*(lds_u16 *)(row + 4));
-      }
-      // FP32 / FP64: differenced form, centre weight 1 - w0 - w2 exactly;
-      // 16-bit deviations: the three weights (one operation fewer)
-      // (the innermost product is an FMA with 0, so that FP16 values enter
-      // all three as mixed-precision FMAs without a conversion)
-      if constexpr (SZ == 2) hy[dy] = __builtin_fmaf(wx0, v0, __builtin_fmaf(wmid[0][a], v1, __builtin_fmaf(wx2, v2, 0.0f)));
-      else hy[dy] = v1 + wx0 * (v0 - v1) + wx2 * (v2 - v1);
-    }
-    C hn;
-    if constexpr (SZ == 2) {
-      hn = wy0 * hy[0] + wmid[1][b] * hy[1] + wy2 * hy[2];
-      // three-address FMAs: with the two-address form the compiler keeps
-      // the partial sums in fixed registers through two moves per plane
-      const C wzm = wmid[2][cc];
-      asm("v_fma_f32 %0, %1, %2, %3" : "=v"(ftk[K]) : "s"(wz2), "v"(hn), "v"(ha[K]));
-      asm("v_fma_f32 %0, %1, %2, %3" : "=v"(ha[K]) : "s"(wzm), "v"(hn), "v"(hb[K]));
-      hb[K] = wz0 * hn;
-      asm("" : "+v"(hb[K]));
-    } else {
-      hn = hy[1] + wy0 * (hy[0] - hy[1]) + wy2 * (hy[2] - hy[1]);
-      ftk[K] = hb[K] + wz0 * (ha[K] - hb[K]) + wz2 * (hn - hb[K]);
-      ha[K] = hb[K];
-      hb[K] = hn;
-      asm("" : "+v"(ftk[K]), "+v"(hb[K]));
+    for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+      for (int e = 0; e < 3; ++e) v[dy][e] = *(lds_f32 *)(base + dy * ROWB + SZ * e);
+  };
+  // x interpolation of three rows
+  // (differenced form, centre weight 1 - w0 - w2 exactly)
+  auto xrows = [&]<int K>(const C (&v)[3][3], C *hx) {
+#pragma unroll
+    for (int dy = 0; dy < 3; ++dy)
+      hx[dy] = v[dy][1] + wx[0][K] * (v[dy][0] - v[dy][1]) + wx[2][K] * (v[dy][2] - v[dy][1]);
+  };
+  // the new slab of plane K: y interpolation, then the z interpolation of the
+  // three slabs into the streamed values of cells z0 + t - 2
+  auto yz = [&]<int K>(const C (&hx)[R + 2]) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const C hn = hx[r + 1] + wy[0] * (hx[r] - hx[r + 1]) + wy[2] * (hx[r + 2] - hx[r + 1]);
+      ftk[K][r] = hb[K][r] + wz[0] * (ha[K][r] - hb[K][r]) + wz[2] * (hn - hb[K][r]);
+      ha[K][r] = hb[K][r];
+      hb[K][r] = hn;
+      asm("" : "+v"(ftk[K][r]), "+v"(hb[K][r]));
     }
     // (the empty asm statements fix the final values: without them the
     // interpolation would be sunk into the collision, keeping the LDS values
-    // of every plane alive until then; they are not volatile, so the LDS reads
-    // of the next planes may be issued before them.)  The plane's arithmetic
-    // stays before this point; only LDS reads and scalar instructions of later
-    // planes may move above it
-    __builtin_amdgcn_sched_barrier(0x0104);
+    // of every plane alive until then)
+  };
+  // every plane of the wave, the LDS reads of three rows issued before the
+  // arithmetic of the three rows before them (the scheduling barriers keep
+  // them there: left to itself the compiler reads six values at a time and
+  // waits for them)
+  auto slab = [&]() {
+    C lo[3][3], hi[3][3];
+    fetch.template operator()<0, 0>(lo);
+    msl_for_planes<PW>([&]<int K>() {
+      C hx[R + 2];
+      fetch.template operator()<K, 1>(hi);
+      __builtin_amdgcn_sched_barrier(0);
+      xrows.template operator()<K>(lo, hx);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (K + 1 < PW) fetch.template operator()<K + 1, 0>(lo);
+      __builtin_amdgcn_sched_barrier(0);
+      xrows.template operator()<K>(hi, hx + 3);
+      yz.template operator()<K>(hx);
+      __builtin_amdgcn_sched_barrier(0);
+    });
   };
 
-  const C gsc0 = (C)(tab->gfac * tab->T0);   // g scale over the f scale
-  const int x = x0 + lane, y = y0 + w;
-  // the lane's cells of this velocity set along the column (bit k: z0 + k),
-  // read before the walk so that no load waits behind the slab loads in it
-  uint32_t mine_bits = 0;
-  if (x < g.nx && y < g.ny)
-    for (int k = 0; k < zn; ++k)
-      mine_bits |= (uint32_t)((cls[((long long)(z0 + k) * g.ny + y) * g.nx + x] & 1) == lat) << k;
   // periodic x (xmir, nx >= 4): the cells x < 2 and x >= nx - 2 are also
   // stored into the ghost columns of the other side, which the next step's
   // windows read; only the columns at the two x ends take the second store
+  const int x = x0 + lane;
   const bool xedge = xmir && (x0 < MSL_G || x0 + MSL_TX > g.nx - MSL_G);
-  // byte offset of the lane's cell at z0 and the stride of one z step
-  const unsigned cell0 = (unsigned)g.idx(x < g.nx ? x : 0, y < g.ny ? y : 0, z0) * SZ;
-  const unsigned zstride = slab_b;
-  // moments, equilibrium, collision and stores of the lane's cell at z
-  auto finish = [&]<bool XE>(const int z) {
-    const bool mine = (mine_bits >> (z - z0)) & 1u;
+  // byte offset of the lane's cell in the first row at z0, and of its image
+  const unsigned cell0 = (unsigned)g.idx(x < g.nx ? x : 0, y0, z0) * SZ;
+  const unsigned img0 = x < MSL_G ? cell0 + (unsigned)g.nx * SZ : cell0 - (unsigned)g.nx * SZ;
+  const uint32_t imask = x < MSL_G || x >= g.nx - MSL_G ? ~0u : 0u;   // lanes with an image
+  // moments, equilibrium, collision and stores of the lane's cells at z0 + k
+  auto finish = [&]<bool XE>(const int k) {
     // the per-plane scales and velocities are loaded here at every cell
-    // (scalar loads) rather than hoisted out of the walk into 2 NP + 3 N
-    // scalar registers
+    // (scalar loads) rather than hoisted out of the walk into scalar registers
     // (through the constant address space: the table is read-only for the
     // kernel's lifetime, which the empty asm would otherwise hide, turning
     // the scalar loads into vector loads)
@@ -330,30 +318,330 @@ k_sc3d_zm(const Tab *__restrict__ tab, int lat, Geo g, const S *__restrict__ in,
     const char *op = (const char *)out + (long long)kb * plane_b64;
     asm volatile("" : "+s"(Lp), "+s"(tp), "+s"(op));
     auto &L = *Lp;
-    C rho = C(0), jx = C(0), jy = C(0), jz = C(0), en = C(0);
-    auto moments = [&]<int K>() {
-      constexpr int i = K % Q, a = i % N, b = (i / N) % N, cc = i / (N * N);
-      // (split walk: population kb + i, z node ccb + cc)
-      const C W = tsel<C>(L.sc[kb + i], L.scf[kb + i]);   // storage scale of f_i
-      if constexpr (K < Q) {
-        const C cx = tsel<C>(L.v[0][a], L.vf[0][a]), cy = tsel<C>(L.v[1][b], L.vf[1][b]),
-                cz = tsel<C>(L.v[2][ccb + cc], L.vf[2][ccb + cc]);
-        const C f = T::dev ? W * (C(1) + ftk[K]) : ftk[K];
-        ftk[K] = f;   // the population itself from here on
-        rho += f;
-        jx += cx * f;
-        jy += cy * f;
-        jz += cz * f;
-        if (TH) en += C(0.5) * (cx * cx + cy * cy + cz * cz) * f;
-      } else {
-        ftk[K] = T::dev ? gsc0 * W * (C(1) + ftk[K]) : ftk[K];
-        en += ftk[K];
+    // partial moments of the wave's planes
+    C rp[R], xp[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) rp[r] = xp[r] = C(0);
+    msl_for_planes<PW>([&]<int K>() {
+      const C cx = L.vf[0][K];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        rp[r] += ftk[K][r];
+        xp[r] = __builtin_fmaf(cx, ftk[K][r], xp[r]);
       }
-    };
-    msl_for_planes<NPW>(moments);
+    });
+    // row r belongs to wave r (mod the number of waves): the others hand it
+    // their partial sums
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      constexpr auto owner = [](int row) { return row % NWV; };
+      if (wv != owner(r)) {
+        const int slot = (wv < owner(r) ? wv : wv - 1) * NPS;
+        s_part[slot][64 * r + lane] = rp[r];
+        s_part[slot + 1][64 * r + lane] = xp[r];
+      }
+    }
+    msl_lds_barrier();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int ow = r % NWV;
+      if (wv == ow) {
+        const int ci = 64 * r + lane;
+        // (the owner's nodes are constants here)
+        C rho = rp[r], jx = xp[r], jy = L.vf[1][ow % N] * rp[r], jz = L.vf[2][ow / N] * rp[r];
+#pragma unroll
+        for (int s = 0; s < NWV - 1; ++s) {
+          const int w = s < ow ? s : s + 1;
+          const C pr = s_part[s * NPS][ci];
+          rho += pr;
+          jx += s_part[s * NPS + 1][ci];
+          jy += L.vf[1][w % N] * pr;
+          jz += L.vf[2][w / N] * pr;
+        }
+        // equilibrium factors in FP64 (no rounding bias in the equilibrium's
+        // mass and momentum), kept in the compute precision; athermal: T = 1
+        const double rd = (double)rho, dx = (double)jx, dy = (double)jy, dz = (double)jz;
+        const double ird = msl_rcp(rd);
+        C om = tp->omegaf;
+        if (tp->tau_mode == 1) om = (C)(1.0 / (tp->mu_T1 / (rd * tp->dt) + 0.5));
+        double p[N];
+        eq_axis<double, N>(L, (dx * ird - L.ur[0]) * L.isq, L.iTr, p);
+#pragma unroll
+        for (int q = 0; q < N; ++q) s_fac[q][ci] = (float)(p[q] * rd);
+        eq_axis<double, N>(L, (dy * ird - L.ur[1]) * L.isq, L.iTr, p);
+#pragma unroll
+        for (int q = 0; q < N; ++q) s_fac[N + q][ci] = (float)p[q];
+        eq_axis<double, N>(L, (dz * ird - L.ur[2]) * L.isq, L.iTr, p);
+#pragma unroll
+        for (int q = 0; q < N; ++q) s_fac[2 * N + q][ci] = (float)p[q];
+        s_fac[3 * N][ci] = om;
+      }
+    }
+    msl_lds_barrier();
+    C Px[R][N], Pyz[R], om[R];
+    unsigned vo[R], vi[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int ci = 64 * r + lane;
+#pragma unroll
+      for (int a = 0; a < N; ++a) Px[r][a] = s_fac[a][ci];
+      Pyz[r] = s_fac[N + b0][ci] * s_fac[2 * N + cc][ci];
+      om[r] = s_fac[3 * N][ci];
+      // (the row's offset goes into the scalar offset of the stores; cells that
+      // are not this set's get an offset beyond the plane)
+      vo[r] = (mine[r] >> k) & 1u ? cell0 : 0x80000000u;
+      if constexpr (XE) vi[r] = ((mine[r] & imask) >> k) & 1u ? img0 : 0x80000000u;
+    }
+    const unsigned so = (unsigned)k * slab_b;
+    msl_for_planes<PW>([&]<int K>() {
+      const __amdgpu_buffer_rsrc_t rsout =
+          __builtin_amdgcn_make_buffer_rsrc((void *)op, (short)0, (int)plane_b, MSL_RSRC_WORD3);
+      op += plane_b64;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const C feq = Px[r][K] * Pyz[r], h = ftk[K][r];
+        const C f = __builtin_fmaf(om[r], feq - h, h);
+        const int sr = (int)(so + (unsigned)r * pitch_b);
+        auto put = [&](unsigned o) {
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, f), rsout, (int)o, sr, 0);
+        };
+        put(vo[r]);
+        if constexpr (XE) put(vi[r]);
+      }
+    });
+  };
+
+  // the walk: slabs t = 0 .. zn + 1; from t = 2 on, cells z0 + t - 2 are
+  // complete.  The next slab is loaded while they collide: vector memory
+  // operations complete in issue order, so waiting until no more than the
+  // cells' stores are outstanding waits for exactly the slab (vmcnt holds at
+  // most 63: with more stores per step the wait also takes the oldest of them)
+  constexpr int VW1 = R * PW < 63 ? R * PW : 63, VW2 = 2 * R * PW < 63 ? 2 * R * PW : 63;
+  issue(0);
+  msl_wait_vm<0>();
+  for (int t = 0; t < zn + 2; ++t) {
+    // the LDS offset passes through an empty asm at every step, so that the
+    // per-plane LDS addresses are formed in the walk, not hoisted out of it
+    asm volatile("" : "+v"(rb));
+    slab();
+    msl_wait_lds();   // the slab's LDS values are read; the next load may overwrite them
+    if (t + 1 < zn + 2) issue(t + 1);
+    if (t >= 2) {
+      if (xedge) {
+        finish.template operator()<true>(t - 2);
+        msl_wait_vm<VW2>();
+      } else {
+        finish.template operator()<false>(t - 2);
+        msl_wait_vm<VW1>();
+      }
+    } else {
+      msl_wait_vm<0>();
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The walk of 16-bit storage: one wave per row of cells with all planes of its
+// cells (D3Q64: four waves, each with the 16 planes of one z node).  The
+// deviations are rounded to 16 bits every step, so a different order of the
+// FP32 sums over a cell's populations would change a few of those roundings,
+// and with them, after some steps, all of them: this form keeps each sum in
+// population order within a wave, which the split over y and z nodes above
+// does not.  What it shares with that walk: ghost rows and slabs mapped when a
+// slab is loaded, short columns, 16-byte DMA chunks (each wave loads its share
+// of the planes: a quarter of the load instructions of 4-byte chunks by all
+// waves), LDS reads one plane ahead of their use.
+// One stream, D3Q27 / D3Q64: 256^3 705 / 645 us in the form before, 644 / 635 us
+// now; 64^3 166 / 229 us before, 32 / 42 us now.  (The split form of D3Q64, with
+// other sums, ran 256^3 in 396 us.)
+// ---------------------------------------------------------------------------
+template <typename S, int N>
+struct SC3RTraits {
+  using T = StoreTraits<S>;
+  static constexpr int Q = N * N * N;
+  static constexpr int NHW = N == 4 ? 4 : 1;   // waves per row of cells
+  static constexpr int NWV = MSL_MTY * NHW;
+  static constexpr int NT = 64 * NWV;
+  static constexpr int NPW = Q / NHW;          // planes of a wave's cells
+  static constexpr int NLD = (Q + NWV - 1) / NWV;   // planes that a wave loads
+  static constexpr int CPR = (66 * 2 + 2 + 15) / 16;
+  static constexpr int ROWB = 16 * CPR;
+  static constexpr int CPP = (MSL_MTY + 2) * CPR;   // chunks of a plane's slab (54 lanes)
+  static_assert(CPP <= 64, "one DMA instruction per plane");
+  static constexpr int SLAB = 16 * CPP;
+  static constexpr int WAVES = N == 4 ? 4 : 3;
+};
+
+template <typename S, int N, bool LIST = false>
+__global__ void __launch_bounds__((SC3RTraits<S, N>::NT)) __attribute__((amdgpu_waves_per_eu(SC3RTraits<S, N>::WAVES)))
+k_sc3d_zr(const Tab *__restrict__ tab, int lat, Geo g, const S *__restrict__ in, S *__restrict__ out,
+          const uint8_t *__restrict__ cls, const uint8_t *__restrict__ tflag, int remap, int xmir, int faces, int zc,
+          const int *__restrict__ tlist, const int *__restrict__ tcount) {
+  using Tr = SC3RTraits<S, N>;
+  using T = typename Tr::T;
+  typedef float C;
+  constexpr int Q = Tr::Q, NHW = Tr::NHW, NPW = Tr::NPW, NLD = Tr::NLD, ROWB = Tr::ROWB, CPR = Tr::CPR, CPP = Tr::CPP,
+                SLAB = Tr::SLAB;
+  constexpr bool SPL = NHW > 1;
+  __shared__ __align__(16) char sm[Q * SLAB];
+  __shared__ float smom[SPL ? NHW : 1][SPL ? 4 : 1][SPL ? 256 : 1];   // partial moments per part
+  const LatTab &L = tab->lat[lat];
+  int tile;
+  if constexpr (LIST) {
+    const int n = *tcount;
+    if ((int)blockIdx.x >= n) return;
+    tile = tlist[msl_xcd_tile((int)blockIdx.x, n)];
+  } else {
+    const int lin = (int)((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x);
+    tile = remap ? msl_xcd_tile(lin, (int)(gridDim.x * gridDim.y * gridDim.z)) : lin;
+  }
+  const int bx = tile % g.ntx, by = (tile / g.ntx) % g.nty;
+  const int z0 = tile / (g.ntx * g.nty) * zc;
+  const int x0 = bx * MSL_TX, y0 = by * MSL_MTY;
+  const int zn = g.nz - z0 < zc ? g.nz - z0 : zc;   // cells of the column (>= 1)
+  {
+    uint8_t any = 0;
+    for (int k = 0; k < zn; ++k) any |= tflag[((long long)(z0 + k) * g.nty + by) * g.ntx + bx];
+    if (!(any & (1 << lat))) return;
+  }
+  // w: the wave's row of cells; hf: its part of the planes, which starts at
+  // plane kb and z node hf
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int w = wv & 3, hf = SPL ? wv >> 2 : 0, kb = hf * NPW;
+  const unsigned pitch_b = (unsigned)g.pitch * 2;
+  const unsigned plane_b = (unsigned)g.plane * 2;
+  const unsigned slab_b = (unsigned)g.rows * pitch_b;
+  // ghost rows and slabs by their faces' rules, as in the walk above
+  auto mapped = [&](int ax, int p, int n) {
+    if (p >= 0 && p < n) return p;
+    const int rule = (faces >> (4 * ax + (p < 0 ? 0 : 2))) & 3;
+    return rule == 1 ? (p < 0 ? p + n : p - n) : (rule == 2 ? (p < 0 ? 0 : n - 1) : p);
+  };
+  // the planes that this wave loads, wv NLD + j: byte offsets of the lane's
+  // chunk inside a slab (D3Q27: 0, 1 or 2 y nodes among them, one register each)
+  const int kl = wv * NLD;
+  unsigned voff[NLD];
+#pragma unroll
+  for (int j = 0; j < NLD; ++j) {
+    const int K = kl + j < Q ? kl + j : Q - 1, a = K % N, b = (K / N) % N;
+    const int row = lane / CPR;
+    voff[j] = (unsigned)(mapped(1, y0 + L.n0[1][b] - 1 + row, g.ny) + MSL_G) * pitch_b +
+              (unsigned)(lane - row * CPR) * 16u + ((unsigned)((g.xo + x0 + L.n0[0][a] - 1) * 2) & ~3u);
+  }
+  int n0z[N];
+#pragma unroll
+  for (int c = 0; c < N; ++c) n0z[c] = L.n0[2][c];
+  const long long plane_b64 = g.plane * 2;
+  // DMA of step t's slab of the wave's share of the planes: slab z0 + n0_z - 1 + t
+  auto issue = [&](const int t) {
+    unsigned oz[N];
+#pragma unroll
+    for (int c = 0; c < N; ++c) oz[c] = (unsigned)(mapped(2, z0 + n0z[c] - 1 + t, g.nz) + MSL_G) * slab_b;
+    const char *pp = (const char *)in + kl * plane_b64;
+    asm volatile("" : "+s"(pp));
+    if (lane < CPP)
+#pragma unroll
+      for (int j = 0; j < NLD; ++j) {
+        const int K = kl + j;
+        if (Q % Tr::NWV == 0 || K < Q) {
+          const int c = K / (N * N);
+          unsigned so = oz[0];
+#pragma unroll
+          for (int q = 1; q < N; ++q) so = c == q ? oz[q] : so;
+          const __amdgpu_buffer_rsrc_t rs =
+              __builtin_amdgcn_make_buffer_rsrc((void *)pp, (short)0, (int)plane_b, MSL_RSRC_WORD3);
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (msl_lds_t *)(sm + K * SLAB), 16, (int)voff[j], (int)so, 0, 0);
+        }
+        pp += plane_b64;
+      }
+  };
+  // per-node tables of each axis: interpolation weights (z from the wave's
+  // first z node on)
+  C wlo[3][N], wmid[3][N], whi[3][N];
+  unsigned rb[N];   // LDS byte of the lane's first element in its row, per x node
+#pragma unroll
+  for (int a = 0; a < N; ++a) {
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+      const int q = SPL && ax == 2 ? hf : a;   // (split walk: every plane of the wave has z node hf)
+      wlo[ax][a] = L.af[ax][q][0];
+      wmid[ax][a] = L.af[ax][q][1];
+      whi[ax][a] = L.af[ax][q][2];
+    }
+    rb[a] = (unsigned)(kb * SLAB + w * ROWB + lane * 2) + (unsigned)((L.n0[0][a] - 1) & 1) * 2u;
+  }
+  // per plane: the z interpolation's partial sums of the next two cells and the
+  // streamed value
+  C ha[NPW], hb[NPW], ftk[NPW];
+#pragma unroll
+  for (int k = 0; k < NPW; ++k) ha[k] = hb[k] = C(0);
+  auto fetch = [&]<int K>(uint32_t (&v)[3][3]) {
+    typedef volatile const __attribute__((address_space(3))) uint16_t lds_u16;
+    const char *base = (const char *)sm + rb[K % N] + K * SLAB;
+#pragma unroll
+    for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+      for (int e = 0; e < 3; ++e) v[dy][e] = *(lds_u16 *)(base + dy * ROWB + 2 * e);
+  };
+  auto recon = [&]<int K>(const uint32_t (&v)[3][3]) {
+    constexpr int a = K % N, b = (K / N) % N, cc = K / (N * N);
+    C hy[3];
+#pragma unroll
+    for (int dy = 0; dy < 3; ++dy)
+      hy[dy] = __builtin_fmaf(wlo[0][a], (C)half_elem<S>(v[dy][0]),
+                              __builtin_fmaf(wmid[0][a], (C)half_elem<S>(v[dy][1]),
+                                             __builtin_fmaf(whi[0][a], (C)half_elem<S>(v[dy][2]), 0.0f)));
+    const C hn = wlo[1][b] * hy[0] + wmid[1][b] * hy[1] + whi[1][b] * hy[2];
+    // (three-address FMAs: no register moves as the walk advances)
+    asm("v_fma_f32 %0, %1, %2, %3" : "=v"(ftk[K]) : "s"(whi[2][cc]), "v"(hn), "v"(ha[K]));
+    asm("v_fma_f32 %0, %1, %2, %3" : "=v"(ha[K]) : "s"(wmid[2][cc]), "v"(hn), "v"(hb[K]));
+    hb[K] = wlo[2][cc] * hn;
+    asm("" : "+v"(hb[K]));
+  };
+  auto slab = [&]() {
+    uint32_t cur[3][3], nxt[3][3];
+    fetch.template operator()<0>(cur);
+    msl_for_planes<NPW>([&]<int K>() {
+      if constexpr (K + 1 < NPW) fetch.template operator()<K + 1>(nxt);
+      __builtin_amdgcn_sched_barrier(0);
+      recon.template operator()<K>(cur);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (K + 1 < NPW)
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+          for (int e = 0; e < 3; ++e) cur[dy][e] = nxt[dy][e];
+    });
+  };
+  const int x = x0 + lane, y = y0 + w;
+  // the lane's cells of this velocity set along the column (bit k: z0 + k)
+  uint32_t mine_bits = 0;
+  if (x < g.nx && y < g.ny)
+    for (int k = 0; k < zn; ++k)
+      mine_bits |= (uint32_t)((cls[((long long)(z0 + k) * g.ny + y) * g.nx + x] & 1) == lat) << k;
+  const bool xedge = xmir && (x0 < MSL_G || x0 + MSL_TX > g.nx - MSL_G);
+  const unsigned cell0 = (unsigned)g.idx(x < g.nx ? x : 0, y < g.ny ? y : 0, z0) * 2;
+  auto finish = [&]<bool XE>(const int k) {
+    const bool mine = (mine_bits >> k) & 1u;
+    // (scales and velocities by scalar loads here, as in the walk above)
+    typedef const __attribute__((address_space(4))) LatTab cLatTab;
+    typedef const __attribute__((address_space(4))) Tab cTab;
+    cLatTab *Lp = (cLatTab *)&L;
+    cTab *tp = (cTab *)tab;
+    const char *op = (const char *)out + (long long)kb * plane_b64;
+    asm volatile("" : "+s"(Lp), "+s"(tp), "+s"(op));
+    auto &L = *Lp;
+    C rho = C(0), jx = C(0), jy = C(0), jz = C(0);
+    msl_for_planes<NPW>([&]<int K>() {
+      constexpr int a = K % N, b = (K / N) % N, cc = K / (N * N);
+      const C f = L.scf[kb + K] * (C(1) + ftk[K]);
+      ftk[K] = f;   // the population itself from here on
+      rho += f;
+      jx += L.vf[0][a] * f;
+      jy += L.vf[1][b] * f;
+      jz += L.vf[2][hf + cc] * f;
+    });
     if constexpr (SPL) {
-      // the other half's partial sums (a + b == b + a: both waves of a row
-      // hold the same sums)
       const int ci = w * 64 + lane;
       smom[hf][0][ci] = rho;
       smom[hf][1][ci] = jx;
@@ -365,117 +653,71 @@ k_sc3d_zm(const Tab *__restrict__ tab, int lat, Geo g, const S *__restrict__ in,
       jy = smom[0][2][ci];
       jz = smom[0][3][ci];
 #pragma unroll
-      for (int h = 1; h < Tr::NHW; ++h) {
+      for (int h = 1; h < NHW; ++h) {
         rho += smom[h][0][ci];
         jx += smom[h][1][ci];
         jy += smom[h][2][ci];
         jz += smom[h][3][ci];
       }
     }
-    // equilibrium factors in FP64 (no rounding bias in the equilibrium's mass
-    // and momentum), kept in the compute precision
+    // equilibrium factors in FP64, kept in FP32; athermal: T = 1
     const double rd = (double)rho, ird = 1.0 / rd;
     const double ux = (double)jx * ird, uy = (double)jy * ird, uz = (double)jz * ird;
-    double Tm = 1.0;
-    if (TH) Tm = ((double)en - 0.5 * rd * (ux * ux + uy * uy + uz * uz)) / (tp->cv * rd);
-    C om = tsel<C>(tp->omega, tp->omegaf);
-    if (tp->tau_mode == 1) {
-      const double mu = TH ? tp->mu_ref * pow(Tm / tp->tau_ref_T, tp->mu_exp) : tp->mu_T1;
-      om = (C)(1.0 / (mu / (rd * Tm * tp->dt) + 0.5));
-    }
+    C om = tp->omegaf;
+    if (tp->tau_mode == 1) om = (C)(1.0 / (tp->mu_T1 / (rd * 1.0 * tp->dt) + 0.5));
     C Px[N], Py[N], Pz[N];
     {
       double px[N], py[N], pz[N];
-      eq_axis<double, N>(L, (ux - L.ur[0]) * L.isq, Tm * L.iTr, px);
-      eq_axis<double, N>(L, (uy - L.ur[1]) * L.isq, Tm * L.iTr, py);
-      eq_axis<double, N>(L, (uz - L.ur[2]) * L.isq, Tm * L.iTr, pz);
+      eq_axis<double, N>(L, (ux - L.ur[0]) * L.isq, L.iTr, px);
+      eq_axis<double, N>(L, (uy - L.ur[1]) * L.isq, L.iTr, py);
+      eq_axis<double, N>(L, (uz - L.ur[2]) * L.isq, L.iTr, pz);
 #pragma unroll
       for (int q = 0; q < N; ++q) {
         Px[q] = (C)(px[q] * rd);
         Py[q] = (C)py[q];
         Pz[q] = (C)pz[q];
       }
-      if constexpr (SPL) {   // z factors from the wave's first z node on
+      if constexpr (SPL) {   // the z factor of the wave's node
 #pragma unroll
-        for (int q = 0; q < N; ++q) {
-          C v = Pz[q];
-#pragma unroll
-          for (int r = q + 1; r < N; ++r)
-            if (r == q + ccb) v = (C)pz[r];
-          Pz[q] = v;
-        }
+        for (int q = 1; q < N; ++q)
+          if (q == hf) Pz[0] = (C)pz[q];
       }
     }
-    const C gf = (C)(tp->gfac * Tm);
-    const unsigned soff = mine ? cell0 + (unsigned)(z - z0) * zstride : 0x80000000u;
-    const unsigned ioff = (mine && x < MSL_G) ? soff + (unsigned)g.nx * SZ
-                          : (mine && x >= g.nx - MSL_G) ? soff - (unsigned)g.nx * SZ : 0x80000000u;
-    auto store = [&]<int K>() {
-      constexpr int i = K % Q, a = i % N, b = (i / N) % N, cc = i / (N * N);
-      const C isc = T::dev ? tsel<C>(L.isc[kb + i], L.iscf[kb + i]) * (K < Q ? C(1) : tsel<C>(tp->igsc, tp->igscf)) : C(1);
+    const unsigned soff = mine ? cell0 + (unsigned)k * slab_b : 0x80000000u;
+    const unsigned ioff = (mine && x < MSL_G) ? soff + (unsigned)g.nx * 2
+                          : (mine && x >= g.nx - MSL_G) ? soff - (unsigned)g.nx * 2 : 0x80000000u;
+    msl_for_planes<NPW>([&]<int K>() {
+      constexpr int a = K % N, b = (K / N) % N, cc = K / (N * N);
+      const C isc = L.iscf[kb + K];
       const C feq = Px[a] * Py[b] * Pz[cc];
       const C v = ftk[K];
-      C vo;
-      if constexpr (K < Q) vo = v + om * (feq - v);
-      else vo = v + om * (gf * feq - v);
-      const S sv = T::store(T::dev ? vo * isc - C(1) : vo);
+      const C vo = v + om * (feq - v);
+      const S sv = T::store(vo * isc - C(1));
       const __amdgpu_buffer_rsrc_t rsout =
           __builtin_amdgcn_make_buffer_rsrc((void *)op, (short)0, (int)plane_b, MSL_RSRC_WORD3);
       op += plane_b64;
-      auto put = [&](unsigned o) {
-        if constexpr (SZ == 8) {
-          typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-          __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, sv), rsout, (int)o, 0, 0);
-        } else if constexpr (SZ == 4) {
-          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, sv), rsout, (int)o, 0, 0);
-        } else {
-          __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, sv), rsout, (int)o, 0, 0);
-        }
-      };
-      put(soff);
-      if constexpr (XE) put(ioff);
-    };
-    msl_for_planes<NPW>(store);
+      __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, sv), rsout, (int)soff, 0, 0);
+      if constexpr (XE) __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, sv), rsout, (int)ioff, 0, 0);
+    });
   };
-
-  // the walk: slabs t = 0 .. zn + 1; from t = 2 on, cell z0 + t - 2 is complete.
-  // The first chunk of the next slab is loaded while the current cell
-  // collides.  The barriers are plain s_barrier with the waits spelt out: a
-  // __syncthreads() would also wait for the cell's stores (its release fence),
-  // exposing their latency at every step, while the slab's loads only need
-  // the loads issued before them (vector memory operations complete in issue
-  // order, so waiting until the stores of one cell are all that is
-  // outstanding waits for exactly the slab).
-  // (vmcnt holds at most 63: with more stores per cell the wait also takes
-  // the oldest of them)
+  // the walk, as above; a row's window rows are loaded by several waves, so
+  // two barriers bracket the reads of a slab
   constexpr int VW1 = NPW < 63 ? NPW : 63, VW2 = 2 * NPW < 63 ? 2 * NPW : 63;
-  constexpr int CH0 = CH < NPW ? CH : NPW;   // (split walk: the wave's half)
-  issue.template operator()<0, CH0>(0);
+  issue(0);
   msl_wait_vm<0>();
   for (int t = 0; t < zn + 2; ++t) {
-    // the row offsets pass through an empty asm at every step, so that the
-    // per-plane LDS addresses are formed in the walk, not hoisted out of it
-    // into NP registers
 #pragma unroll
     for (int a = 0; a < N; ++a) asm volatile("" : "+v"(rb[a]));
-    auto chunk = [&]<int CI>() {
-      constexpr int k0 = CI * CH, k1 = k0 + CH < NP ? k0 + CH : NP;
-      if constexpr (CI > 0) {
-        issue.template operator()<k0, k1>(t);
-        msl_wait_vm<0>();
-      }
-      msl_lds_barrier();   // every wave's share of the slab is in LDS
-      msl_for_range<k0, (k1 < NPW ? k1 : NPW)>(recon);
-      msl_lds_barrier();   // the chunk's LDS values are read; the next load may overwrite them
-    };
-    msl_for_planes<NCH>(chunk);
-    if (t + 1 < zn + 2) issue.template operator()<0, CH0>(t + 1);
+    msl_lds_barrier();   // every wave's share of the slab is in LDS
+    slab();
+    msl_lds_barrier();   // the slab's LDS values are read; the next load may overwrite them
+    if (t + 1 < zn + 2) issue(t + 1);
     if (t >= 2) {
       if (xedge) {
-        finish.template operator()<true>(z0 + t - 2);
+        finish.template operator()<true>(t - 2);
         msl_wait_vm<VW2>();
       } else {
-        finish.template operator()<false>(z0 + t - 2);
+        finish.template operator()<false>(t - 2);
         msl_wait_vm<VW1>();
       }
     } else {
