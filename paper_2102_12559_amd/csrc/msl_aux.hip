@@ -74,60 +74,6 @@ __device__ __forceinline__ long long pass_cells(const Geo &g, int ax, int *ext, 
   return tot;
 }
 
-// 2D: periodic and zero-gradient ghosts of every axis in one launch (the
-// step of a small 2D grid is latency-bound: one launch instead of two); one
-// thread per (ghost cell, plane).  A ghost cell belongs to the pass of its highest
-// out-of-range axis (that axis' ghost layers, lower axes with their ghosts,
-// higher axes interior), so the passes partition the ghost cells.  A cell
-// whose owning face is a copy rule takes the value at the point where every
-// out-of-range coordinate is mapped by its own face's rule (wrap, clamp),
-// except fixed and diffuse faces of lower axes, whose ghost coordinate is
-// kept (constant ghosts, or diffuse ghosts filled earlier in the step): the
-// same values as filling the axes one after the other.
-template <typename S>
-__global__ void __launch_bounds__(AUX_BLOCK)
-k_bc_copy(const Tab *__restrict__ tab, Geo g, BCArgs b, char *bl, char *bh, int np0) {
-  // blockIdx.y: plane; x: ghost cell, passes in axis order (32-bit indexing:
-  // the ghost layers of any admissible grid hold fewer than 2^31 cells)
-  const int N[3] = {g.nx, g.ny, g.nz};
-  int ext[3][3], lo[3][3], cnt[3] = {0, 0, 0};
-  for (int a = 0; a < g.dim; ++a) {
-    cnt[a] = 1;
-    for (int e = 0; e < 3; ++e) {
-      if (e >= g.dim) { ext[a][e] = 1; lo[a][e] = 0; }
-      else if (e < a) { ext[a][e] = N[e] + 2 * MSL_G; lo[a][e] = -MSL_G; }
-      else if (e == a) { ext[a][e] = 2 * MSL_G; lo[a][e] = 0; }
-      else { ext[a][e] = N[e]; lo[a][e] = 0; }
-      cnt[a] *= ext[a][e];
-    }
-  }
-  int cellid = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (cellid >= cnt[0] + cnt[1] + cnt[2]) return;
-  const int plane = (int)blockIdx.y;
-  int ax = 0;
-  while (cellid >= cnt[ax]) cellid -= cnt[ax++];
-  int p[3];
-  int r = cellid;
-  for (int e = 0; e < 3; ++e) {
-    p[e] = lo[ax][e] + r % ext[ax][e];
-    r /= ext[ax][e];
-  }
-  const int gi = p[ax];
-  const int side = gi < MSL_G ? 0 : 1;
-  p[ax] = side ? N[ax] + (gi - MSL_G) : gi - MSL_G;
-  const int rule = b.bc[2 * ax + side];
-  if (rule != MSL_BC_PERIODIC && rule != MSL_BC_OUTFLOW_ZG) return;
-  int q[3] = {p[0], p[1], p[2]};
-  for (int a = 0; a <= ax; ++a) {
-    if (q[a] >= 0 && q[a] < N[a]) continue;
-    const int ra = b.bc[2 * a + (q[a] < 0 ? 0 : 1)];
-    if (ra == MSL_BC_PERIODIC) q[a] = q[a] < 0 ? q[a] + N[a] : q[a] - N[a];
-    else if (ra == MSL_BC_OUTFLOW_ZG) q[a] = q[a] < 0 ? 0 : N[a] - 1;
-  }
-  S *pl = plane < np0 ? (S *)bl + (long long)plane * g.plane : (S *)bh + (long long)(plane - np0) * g.plane;
-  pl[g.idx(p[0], p[1], p[2])] = pl[g.idx(q[0], q[1], q[2])];
-}
-
 // 3D: periodic and zero-gradient ghosts, one axis after the other: x, then y,
 // then z.  A ghost takes the value at the point where its out-of-range
 // coordinate is mapped by its face's rule (wrap, clamp).  The x pass covers
@@ -241,28 +187,32 @@ k_bc_fixed(const Tab *__restrict__ tab, Geo g, int ax, BCArgs b, char *bl, char 
 // diffuse walls (every step): the ghost holds the wall equilibrium scaled so
 // that as many particles leave the wall as arrive at it from the adjacent
 // fluid cell (zero net wall-normal mass flux).  The unit-density equilibrium
-// and its outgoing flux come from the tables; a thread reads only the arriving
-// populations of its adjacent cell and writes every plane of its ghost cell.
+// and its outgoing flux come from the tables.  A workgroup takes 16 wall
+// columns: 16 threads of each share out the arriving populations of the
+// adjacent cell (their sums meet in LDS) and then the planes of both sets, in
+// both ghost layers.  One thread per ghost cell, its populations one after the
+// other, took 22 us on an 8 x 64 channel, all of it latency; this 2 to 3 us.
+#define DIFF_COLS 16
 template <typename S>
 __global__ void __launch_bounds__(AUX_BLOCK)
 k_bc_diffuse(const Tab *__restrict__ tab, Geo g, int ax, BCArgs b, char *bl, char *bh,
              const uint8_t *__restrict__ cls) {
+  constexpr int PARTS = AUX_BLOCK / DIFF_COLS;
+  __shared__ double s_in[PARTS][DIFF_COLS];
   const int N[3] = {g.nx, g.ny, g.nz};
-  int ext[3], lo[3];
-  const long long tot = pass_cells(g, ax, ext, lo);
-  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= tot) return;
-  int p[3];
-  long long r = t;
+  const int col = threadIdx.x % DIFF_COLS, part = threadIdx.x / DIFF_COLS;
+  // the wall column: lower axes with their ghosts, higher axes interior, side
+  long long r = (long long)blockIdx.x * DIFF_COLS + col;
+  int p[3] = {0, 0, 0};
+#pragma unroll
   for (int a = 0; a < 3; ++a) {
-    p[a] = lo[a] + (int)(r % ext[a]);
-    r /= ext[a];
+    if (a >= g.dim || a == ax) continue;
+    const int ext = a < ax ? N[a] + 2 * MSL_G : N[a];
+    p[a] = (int)(r % ext) - (a < ax ? MSL_G : 0);
+    r /= ext;
   }
-  const int gi = p[ax];
-  const int side = gi < MSL_G ? 0 : 1;
-  p[ax] = side ? N[ax] + (gi - MSL_G) : gi - MSL_G;
-  const int face = 2 * ax + side;
-  if (b.bc[face] != MSL_BC_DIFFUSE_WALL) return;
+  const int side = (int)r, face = 2 * ax + (side & 1);
+  const bool live = r < 2 && b.bc[face] == MSL_BC_DIFFUSE_WALL;
   // adjacent fluid point; lower-axis ghosts map through their own rule
   int q[3] = {p[0], p[1], p[2]};
   q[ax] = side ? N[ax] - 1 : 0;
@@ -274,31 +224,48 @@ k_bc_diffuse(const Tab *__restrict__ tab, Geo g, int ax, BCArgs b, char *bl, cha
     else if (fr == MSL_BC_OUTFLOW_ZG) q[a] = q[a] < 0 ? 0 : N[a] - 1;
     else use_low = 1;
   }
-  const int m = use_low ? 0 : (cls[((long long)q[2] * g.ny + q[1]) * g.nx + q[0]] & 1);
-  const LatTab &Lm = tab->lat[m];
-  const S *pm = (const S *)(m ? bh : bl);
-  const int src = g.idx(q[0], q[1], q[2]);
-  const int n = Lm.n;
-  const int stride = ax == 0 ? 1 : (ax == 1 ? n : n * n);
-  // populations arriving at the wall: v_ax < 0 at the lower face, > 0 at the upper
+  int m = 0;
   double in = 0;
-  for (int i = 0; i < Lm.Q; ++i) {
-    const double cn = Lm.v[ax][(i / stride) % n];
-    if (side ? cn > 0 : cn < 0)
-      in += fabs(cn) * load_pop<S>(pm + (long long)i * g.plane, src, Lm.sc[i]);
+  if (live) {
+    m = use_low ? 0 : (cls[((long long)q[2] * g.ny + q[1]) * g.nx + q[0]] & 1);
+    const LatTab &Lm = tab->lat[m];
+    const S *pm = (const S *)(m ? bh : bl);
+    const int src = g.idx(q[0], q[1], q[2]), n = Lm.n, stride = ax == 0 ? 1 : (ax == 1 ? n : n * n);
+    // populations arriving at the wall: v_ax < 0 at the lower face, > 0 at the upper
+#pragma unroll
+    for (int j = 0; j < MSL_MAXQ / PARTS; ++j) {
+      const int i = part + PARTS * j;
+      if (i >= Lm.Q) break;
+      const double cn = Lm.v[ax][(i / stride) % n];
+      if (side ? cn > 0 : cn < 0) in += fabs(cn) * load_pop<S>(pm + (long long)i * g.plane, src, Lm.sc[i]);
+    }
   }
+  s_in[part][col] = in;
+  __syncthreads();
+  if (!live) return;
+  in = 0;
+#pragma unroll
+  for (int k = 0; k < PARTS; ++k) in += s_in[k][col];
   const double rw = in / tab->wall_out[face][m];
   const double Tw = b.st[face][4];
-  const int dst = g.idx(p[0], p[1], p[2]);
-  for (int l = 0; l < tab->nlat; ++l) {
+  // the two ghost layers of the wall
+  int dst[MSL_G];
+#pragma unroll
+  for (int d = 0; d < MSL_G; ++d) {
+    p[ax] = side ? N[ax] + d : d - MSL_G;
+    dst[d] = g.idx(p[0], p[1], p[2]);
+  }
+  const int Q0 = tab->lat[0].Q, QT = Q0 + (tab->nlat > 1 ? tab->lat[1].Q : 0);
+  for (int k = part; k < QT; k += PARTS) {
+    const int l = k >= Q0, i = l ? k - Q0 : k;
     const LatTab &L = tab->lat[l];
-    S *pl = (S *)(l ? bh : bl);
-    for (int i = 0; i < L.Q; ++i) {
-      const double f = rw * tab->wall_eq[face][l][i];
-      store_pop<S>(pl + (long long)i * g.plane, dst, f, L.sc[i]);
+    S *pl = (S *)(l ? bh : bl) + (long long)i * g.plane;
+    const double f = rw * tab->wall_eq[face][l][i];
+#pragma unroll
+    for (int d = 0; d < MSL_G; ++d) {
+      store_pop<S>(pl, dst[d], f, L.sc[i]);
       if (tab->thermal)
-        store_pop<S>(pl + (long long)(L.Q + i) * g.plane, dst, tab->gfac * Tw * f,
-                     tab->gfac * tab->T0 * L.sc[i]);
+        store_pop<S>(pl + (long long)L.Q * g.plane, dst[d], tab->gfac * Tw * f, tab->gfac * tab->T0 * L.sc[i]);
     }
   }
 }
@@ -904,9 +871,8 @@ static long long host_pass_cells(const Geo &g, int ax) {
   return tot;
 }
 
-// per step: diffuse walls (from interior cells), then the periodic and
-// zero-gradient copies: 2D in one launch; 3D x (unless the previous step
-// wrote them), y, z
+// per step: diffuse walls (from interior cells), then in 3D the periodic and
+// zero-gradient copies: x (unless the previous step wrote them), y, z
 int msl_launch_bc(msl_ctx *c, char *bl, char *bh) {
   BCArgs b;
   bc_args(c, b);
@@ -922,18 +888,11 @@ int msl_launch_bc(msl_ctx *c, char *bl, char *bh) {
   for (int ax = 0; ax < c->D; ++ax) {
     const int r0 = b.bc[2 * ax], r1 = b.bc[2 * ax + 1];
     if (r0 == MSL_BC_DIFFUSE_WALL || r1 == MSL_BC_DIFFUSE_WALL)
-      DISPATCH_STORE(c, k_bc_diffuse, dim3(nblocks(host_pass_cells(g, ax))), dim3(AUX_BLOCK), c->dtab,
-                     g, ax, b, bl, bh, c->cls);
+      DISPATCH_STORE(c, k_bc_diffuse, dim3((unsigned)((host_pass_cells(g, ax) / MSL_G + DIFF_COLS - 1) / DIFF_COLS)),
+                     dim3(AUX_BLOCK), c->dtab, g, ax, b, bl, bh, c->cls);
   }
   const dim3 blk(AUX_BLOCK);
-  if (c->D == 2) {
-    if (c->zgm) return last_err();   // applied by the stream-collide launches
-    long long tot = 0;
-    for (int ax = 0; ax < 2; ++ax) tot += host_pass_cells(g, ax);
-    if (copies(0) || copies(1))
-      DISPATCH_STORE(c, k_bc_copy, dim3(nblocks(tot), np0 + np1), blk, c->dtab, g, b, bl, bh, np0);
-    return last_err();
-  }
+  if (c->D == 2) return last_err();   // copies: mapped by the stream-collide launches
   const int nz = g.nz;
   if (copies(0) && !c->xg_ok)
     DISPATCH_STORE(c, k_bc_xcopy, dim3(nblocks((long long)2 * MSL_G * g.ny * nz), np0 + np1), blk, g, b,

@@ -572,23 +572,11 @@ int msl_create(const msl_config *cfg, void *ws, size_t bytes, void *stream, msl_
   // in the high-order one)
   const int sc2 = cfg->lift_mode != MSL_LIFT_MLP && msl_stream_sc2_all(c);
   c->fuse = sc2 && c->nlat == 2;
-  // 2D faces that are all zero-gradient or fixed: the zero-gradient ones are
-  // applied inside the stream-collide launches (the fixed ghosts are
-  // constant), so a step launches no ghost fill
-  if (sc2) {
-    int m = 0, ok = 1;
-    for (int f = 0; f < 4; ++f) {
-      if (cfg->bc[f] == MSL_BC_OUTFLOW_ZG) m |= 1 << f;
-      else if (cfg->bc[f] != MSL_BC_FIXED_EQ) ok = 0;
-    }
-    c->zgm = ok ? m : 0;
-  }
-  if (cfg->dim == 3 && !cfg->thermal && cfg->store != MSL_FP64) {
+  if (cfg->dim == 3 && !cfg->thermal && cfg->store != MSL_FP64)
     for (int l = 0; l < c->nlat; ++l)
       if (cfg->store != MSL_FP32 || c->htab.lat[l].n == 3) c->walk_sets |= 1 << l;
-    for (int f = 0; f < 6; ++f)
-      c->walk |= (cfg->bc[f] == MSL_BC_PERIODIC ? 1 : (cfg->bc[f] == MSL_BC_OUTFLOW_ZG ? 2 : 0)) << (2 * f);
-  }
+  for (int f = 0; f < 2 * cfg->dim; ++f)
+    c->faces |= (cfg->bc[f] == MSL_BC_PERIODIC ? 1 : (cfg->bc[f] == MSL_BC_OUTFLOW_ZG ? 2 : 0)) << (2 * f);
   // step graphs: one block per criterion period (at most 64 steps), else 16
   c->gmode = 0;
   c->gB = cfg->crit_kind && cfg->crit_every > 0 && c->nlat > 1 && cfg->crit_every <= 64 ? cfg->crit_every : 16;

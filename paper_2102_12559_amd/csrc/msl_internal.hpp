@@ -168,10 +168,11 @@ struct msl_ctx {
   int xmir, xg_ok;
   // 3D sets that run a column walk (bit l: set l; athermal, 16-bit storage or
   // FP32 D3Q27): the walk maps ghost rows and slabs by the faces' rules itself,
-  // only their ghost columns are filled; walk: two bits per face (1 periodic, 2
-  // zero-gradient, 0 stored ghosts: fixed, diffuse)
+  // only their ghost columns are filled
   int walk_sets;
-  int walk;
+  // two bits per face for the kernels that map ghost points (2D, 3D walks): 1
+  // periodic, 2 zero-gradient, 0 stored ghosts (fixed, diffuse)
+  int faces;
   // live tiles of the high-order set, ascending (sparse stream-collide
   // launches walk this list instead of the whole tile grid); tl_ok: the list
   // matches the current tile flags
@@ -214,10 +215,6 @@ struct msl_ctx {
   // the stream-collide launches convert the band cells themselves (no band
   // conversion launch in a step)
   int fuse;
-  // 2D zero-gradient faces applied by the stream-collide launches to their
-  // staged windows (bits: x low, x high, y low, y high); set when every face
-  // is zero-gradient or fixed, and then no ghost fill runs per step
-  int zgm;
   hipStream_t gs[2];
   hipEvent_t gev[2];
   hipGraphExec_t gx[2];

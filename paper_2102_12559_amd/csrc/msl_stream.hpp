@@ -184,7 +184,7 @@ __device__ __forceinline__ void for_planes(F &&f) {
 template <typename S, bool TH, int N, bool QE = false>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SCTraits<S, TH, N, 2>::WAVES)))
 k_sc2d(const Tab *__restrict__ tab, int lat, Geo g, const S *__restrict__ in, S *__restrict__ out,
-       const uint8_t *__restrict__ cls, const uint8_t *__restrict__ tflag) {
+       const uint8_t *__restrict__ cls, const uint8_t *__restrict__ tflag, int faces) {
   using Tr = SCTraits<S, TH, N, 2>;
   using T = typename Tr::T;
   using C = typename Tr::C;
@@ -205,24 +205,38 @@ k_sc2d(const Tab *__restrict__ tab, int lat, Geo g, const S *__restrict__ in, S 
     if (!(any & (1 << lat))) return;
   }
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  // per-thread offsets of the staged window elements (plane independent)
-  int eoff[NLD];
+  // row and column of the thread's staged window elements
+  int er[NLD], ec[NLD];
 #pragma unroll
   for (int m = 0; m < NLD; ++m) {
     int e = threadIdx.x + 256 * m;
     e = e < NE ? e : NE - 1;
-    const int rr = e / LW, cc = e - rr * LW;
-    eoff[m] = (rr * g.pitch + cc) * (int)sizeof(S);   // byte offset from the window origin
+    er[m] = e / LW;
+    ec[m] = e - er[m] * LW;
   }
+  // ghost points mapped by their faces' rules (as in msl_stream2.hpp): windows
+  // that leave the domain; a stored ghost row keeps its own x ghosts
+  auto mapped = [&](int ax, int p, int n) {
+    if (p >= 0 && p < n) return p;
+    const int rule = (faces >> (4 * ax + (p < 0 ? 0 : 2))) & 3;
+    return rule == 1 ? (p < 0 ? p + n : p - n) : (rule == 2 ? (p < 0 ? 0 : n - 1) : p);
+  };
+  const bool edge = faces && (x0 < MSL_G || x0 + MSL_TX + MSL_G > g.nx || y0 < MSL_G || y0 + TY + MSL_G > g.ny);
   C ft[NP][R];
   C reg[NLD];
   auto gload = [&]<int K>() {
     constexpr int i = K % Q, a = i % N, b = i / N;
     const int ox = L.n0[0][a] - 1, oy = L.n0[1][b] - 1;
-    const S *base = in + (long long)K * g.plane + g.idx(x0 + ox, y0 + oy, 0);
+    const S *base = in + (long long)K * g.plane;
 #pragma unroll
-    for (int m = 0; m < NLD; ++m)
-      reg[m] = (C)T::load(*(const S *)((const char *)base + (unsigned)eoff[m]));
+    for (int m = 0; m < NLD; ++m) {
+      int X = x0 + ox + ec[m], Y = y0 + oy + er[m];
+      if (edge) {
+        Y = mapped(1, Y, g.ny);
+        if (Y >= 0 && Y < g.ny && X < g.nx + MSL_G) X = mapped(0, X, g.nx);
+      }
+      reg[m] = (C)T::load(base[g.idx(X, Y, 0)]);
+    }
   };
   auto lstore = [&](int buf) {
 #pragma unroll
@@ -283,7 +297,7 @@ static int launch_sc2(msl_ctx *c, int lat, const char *in, char *out, char *oth)
     if (small) {
       dim3 grid((g.nx + MSL_TX - 1) / MSL_TX, (g.ny + T2::TY - 1) / T2::TY);
       hipLaunchKernelGGL((k_sc2d_res<S, TH, N, true, false, QE, NO>), grid, block, 0, c->stream, c->dtab, lat, g,
-                         (const S *)in, (S *)out, c->cls, c->tflag, lat == 0, nt, nullptr, nullptr, os, c->zgm);
+                         (const S *)in, (S *)out, c->cls, c->tflag, lat == 0, nt, nullptr, nullptr, os, c->faces);
     }
   }
   if constexpr (N > 3 && NO < N) {
@@ -309,7 +323,7 @@ static int launch_sc2(msl_ctx *c, int lat, const char *in, char *out, char *oth)
       if (c->tl_n == 0) return MSL_OK;
       dim3 grid((unsigned)c->tl_n);
       hipLaunchKernelGGL((k_sc2d_res<S, TH, N, false, true, QE, NO>), grid, block, 0, c->stream, c->dtab, lat,
-                         g, (const S *)in, (S *)out, c->cls, c->tflag, 0, nt, c->tlist, c->tcount, os, c->zgm);
+                         g, (const S *)in, (S *)out, c->cls, c->tflag, 0, nt, c->tlist, c->tcount, os, c->faces);
       return hipGetLastError() == hipSuccess ? MSL_OK : MSL_EHIP;
     }
   }
@@ -317,7 +331,7 @@ static int launch_sc2(msl_ctx *c, int lat, const char *in, char *out, char *oth)
     using T2 = SC2Traits<S, TH, N>;
     dim3 grid((g.nx + MSL_TX - 1) / MSL_TX, (g.ny + T2::TY - 1) / T2::TY);
     hipLaunchKernelGGL((k_sc2d_res<S, TH, N, false, false, QE, NO>), grid, block, 0, c->stream, c->dtab, lat, g,
-                       (const S *)in, (S *)out, c->cls, c->tflag, lat == 0, nt, nullptr, nullptr, os, c->zgm);
+                       (const S *)in, (S *)out, c->cls, c->tflag, lat == 0, nt, nullptr, nullptr, os, c->faces);
   }
   return hipGetLastError() == hipSuccess ? MSL_OK : MSL_EHIP;
 }
@@ -351,7 +365,7 @@ static int launch_one(msl_ctx *c, int lat, const char *in, char *out, char *oth)
     if (oth) return MSL_EINVAL;
     dim3 grid((g.nx + MSL_TX - 1) / MSL_TX, (g.ny + MSL_MTY * Tr::R - 1) / (MSL_MTY * Tr::R));
     hipLaunchKernelGGL((k_sc2d<S, TH, N, QE>), grid, block, 0, c->stream, c->dtab, lat, g,
-                       (const S *)in, (S *)out, c->cls, c->tflag);
+                       (const S *)in, (S *)out, c->cls, c->tflag, c->faces);
   } else {
     if (oth) return MSL_EINVAL;
     if constexpr (msl_walk_set<S, TH>(N)) {
@@ -380,11 +394,11 @@ static int launch_one(msl_ctx *c, int lat, const char *in, char *out, char *oth)
           }
           if (c->tl_n == 0) return MSL_OK;
           hipLaunchKernelGGL(list, dim3((unsigned)c->tl_n), dim3(nt), 0, c->stream, c->dtab, lat, g, (const S *)in,
-                             (S *)out, c->cls, c->tflag, 0, c->xmir, c->walk, zc, c->tlist, c->tcount);
+                             (S *)out, c->cls, c->tflag, 0, c->xmir, c->faces, zc, c->tlist, c->tcount);
         } else {
           dim3 grid((g.nx + MSL_TX - 1) / MSL_TX, (g.ny + MSL_MTY - 1) / MSL_MTY, ncz);
           hipLaunchKernelGGL(dense, grid, dim3(nt), 0, c->stream, c->dtab, lat, g, (const S *)in, (S *)out, c->cls,
-                             c->tflag, lat == 0, c->xmir, c->walk, zc, (const int *)nullptr, (const int *)nullptr);
+                             c->tflag, lat == 0, c->xmir, c->faces, zc, (const int *)nullptr, (const int *)nullptr);
         }
         return hipGetLastError() == hipSuccess ? MSL_OK : MSL_EHIP;
       };
@@ -460,7 +474,7 @@ int msl_launch_store_th(msl_ctx *c, int lat, const char *in, char *out, char *ot
 }
 
 // every set of a 2D context runs the kernel with all planes resident in LDS
-// (which can convert band cells and apply zero-gradient faces itself)
+// (which can convert band cells itself)
 template <typename S, bool TH>
 int msl_sc2_all_th(const msl_ctx *c) {
   if (c->D != 2) return 0;

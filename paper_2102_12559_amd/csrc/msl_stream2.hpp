@@ -115,7 +115,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SC2Tra
 k_sc2d_res(const Tab *__restrict__ tab, int lat, Geo g, const S *__restrict__ in,
            S *__restrict__ out, const uint8_t *__restrict__ cls,
            const uint8_t *__restrict__ tflag, int remap, int nt, const int *__restrict__ tlist,
-           const int *__restrict__ tcount, S *__restrict__ oth, int zgm) {
+           const int *__restrict__ tcount, S *__restrict__ oth, int faces) {
   using Tr = SC2Traits<S, TH, N, SMALL>;
   using T = typename Tr::T;
   using C = typename Tr::C;
@@ -143,31 +143,65 @@ k_sc2d_res(const Tab *__restrict__ tab, int lat, Geo g, const S *__restrict__ in
   const int tx = lane, ty = w;
   const unsigned pitch_b = (unsigned)g.pitch * SZ;
   const unsigned plane_b = (unsigned)g.plane * SZ;
-  // plane-independent byte offsets of this lane's window chunks (16 bytes)
   constexpr int CPR = Tr::CPR, CP = Tr::CP;
-  unsigned voff[M];
+  // Ghost points.  A coordinate outside the domain is mapped by its face's
+  // rule (two bits of `faces` per face: 1 periodic, wrapped; 2 zero-gradient,
+  // clamped; 0 fixed or diffuse, the stored ghost layer) when the windows are
+  // loaded, so no launch copies ghost cells: rows by the lanes' addresses, and
+  // in tiles at an x end the at most four ghost columns of a window row by
+  // loads of their own, which replace what the row's load brought.  The same
+  // values as filling the ghost layers axis by axis.  (The ghost fill took 3.7 us
+  // of a 16 us step on 64^2, 13 to 14 us of one on 3000^2 and 3001 x 2003.)
+  auto mapped = [&](int ax, int p, int n) {
+    if (p >= 0 && p < n) return p;
+    const int rule = (faces >> (4 * ax + (p < 0 ? 0 : 2))) & 3;
+    return rule == 1 ? (p < 0 ? p + n : p - n) : (rule == 2 ? (p < 0 ? 0 : n - 1) : p);
+  };
+  // 1. every plane's window in flight at once (direct-to-LDS loads of 16-byte
+  // chunks): voff holds a chunk's byte offset in a plane, without the plane's
+  // departure offset.  In tiles at a y end with faces to map (a uniform
+  // condition) a chunk has one row address for each of the three y origins.
+  auto issue = [&]<int K>(int soff, auto voff) {
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(in + (long long)K * g.plane), (short)0, (int)plane_b, MSL_RSRC_WORD3);
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+      if ((m + 1) * 256 <= CP || lane + 64 * (w + 4 * m) < CP)   // chunk of the window
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (msl_lds_t *)(sm + K * PD + 256 * (w + 4 * m)), 16,
+                                                 (int)voff(m), soff, 0, 0);
+  };
+  unsigned vrow[M], vcol[M];
 #pragma unroll
   for (int m = 0; m < M; ++m) {
     int d = lane + 64 * (w + 4 * m);
     d = d < CP ? d : CP - 1;
-    const int row = d / CPR, col = d - row * CPR;
-    voff[m] = (unsigned)row * pitch_b + (unsigned)col * 16u;
+    vrow[m] = d / CPR;
+    vcol[m] = (d - vrow[m] * CPR) * 16u;
   }
-  // 1. every plane's window in flight at once (direct-to-LDS loads)
-  auto issue = [&]<int K>() {
-    constexpr int i = K % Q, a = i % N, b = i / N;
-    const int ox = L.n0[0][a] - 1, oy = L.n0[1][b] - 1;
-    const unsigned org = (unsigned)g.idx(x0 + ox, y0 + oy, 0) * SZ;   // window origin (bytes)
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(in + (long long)K * g.plane), (short)0, (int)plane_b, MSL_RSRC_WORD3);
-    const int soff = (int)(org & ~3u);
+  if ((faces >> 4) && (y0 < MSL_G || y0 + TY + MSL_G > g.ny)) {
+    unsigned voff[3][M];
 #pragma unroll
     for (int m = 0; m < M; ++m)
-      if ((m + 1) * 256 <= CP || lane + 64 * (w + 4 * m) < CP)   // chunk of the window
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            rs, (msl_lds_t *)(sm + K * PD + 256 * (w + 4 * m)), 16, (int)voff[m], soff, 0, 0);
-  };
-  msl_for_planes<NP>(issue);
+#pragma unroll
+      for (int o = 0; o < 3; ++o)
+        voff[o][m] = (unsigned)(mapped(1, y0 - MSL_G + o + (int)vrow[m], g.ny) + MSL_G) * pitch_b + vcol[m];
+    msl_for_planes<NP>([&]<int K>() {
+      constexpr int i = K % Q, a = i % N, b = i / N;
+      const int o = L.n0[1][b] + 1;   // window rows start at y0 - 2 + o
+      issue.template operator()<K>((int)((unsigned)((g.xo + x0 + L.n0[0][a] - 1) * SZ) & ~3u), [&](int m) {
+        return o == 0 ? voff[0][m] : (o == 1 ? voff[1][m] : voff[2][m]);
+      });
+    });
+  } else {
+    unsigned voff[M];
+#pragma unroll
+    for (int m = 0; m < M; ++m) voff[m] = vrow[m] * pitch_b + vcol[m];
+    msl_for_planes<NP>([&]<int K>() {
+      constexpr int i = K % Q, a = i % N, b = i / N;
+      const unsigned org = (unsigned)g.idx(x0 + L.n0[0][a] - 1, y0 + L.n0[1][b] - 1, 0) * SZ;   // window origin (bytes)
+      issue.template operator()<K>((int)(org & ~3u), [&](int m) { return voff[m]; });
+    });
+  }
   // band conversion tables of the other set, staged in LDS while the windows
   // load (uniform reads later, no scalar-load round trips in the epilogue):
   // lifting: the Hermite basis of the high-order nodes (NO x NO), the per-axis
@@ -203,58 +237,39 @@ k_sc2d_res(const Tab *__restrict__ tab, int lat, Geo g, const S *__restrict__ in
     mine[r] = inside && (cb & 1) == lat;
     band[r] = NO > 0 && mine[r] && (cb & 2);
   }
-  __syncthreads();   // the compiler waits for the loads before the barrier
-  // zero-gradient faces (bits of zgm: x low, x high, y low, y high) applied to
-  // the staged windows instead of a ghost fill: a ghost takes the value of
-  // the edge cell of its row (x faces), then ghost rows copy the edge row,
-  // x ghosts included (y faces), the order of the separable ghost passes.
-  // Fixed faces keep their stored ghosts.  Only tiles whose windows reach a
-  // ghost layer of such a face take part (a uniform condition).
-  if (zgm && (((zgm & 1) && x0 < MSL_G) || ((zgm & 2) && x0 + MSL_TX + MSL_G > g.nx) ||
-              ((zgm & 4) && y0 < MSL_G) || ((zgm & 8) && y0 + TY + MSL_G > g.ny))) {
-    auto origin = [&](int K, int &wx, int &wy, int &boff) {
-      const int i = K % Q, a = i % N, b = i / N;
-      wx = x0 + L.n0[0][a] - 1;
-      wy = y0 + L.n0[1][b] - 1;
-      boff = (int)(((unsigned)g.idx(wx, wy, 0) * SZ) & 3u);
-    };
-    // x ghosts of the rows inside the domain: (plane, window row, ghost column)
-    if (zgm & 3) {
-      for (int it = threadIdx.x; it < NP * LR * 2 * MSL_G; it += 256) {
-        const int K = it / (LR * 2 * MSL_G), rem = it % (LR * 2 * MSL_G);
-        const int r = rem / (2 * MSL_G), gc = rem % (2 * MSL_G);
-        const int side = gc / MSL_G;
-        if (!(zgm & (1 << side))) continue;
-        int wx, wy, boff;
-        origin(K, wx, wy, boff);
-        const int Y = wy + r;
-        const int X = side ? g.nx + (gc - MSL_G) : gc - MSL_G;
-        const int j = X - wx, js = (side ? g.nx - 1 : 0) - wx;
-        if (Y < 0 || Y >= g.ny || j < 0 || j >= MSL_TX + 2) continue;
-        char *row = (char *)(sm + K * PD + r * LWD) + boff;
-        *(S *)(row + j * SZ) = *(const S *)(row + js * SZ);
-      }
-      __syncthreads();
+  // tiles at an x end (a uniform condition): the ghost columns X = -2, -1, nx,
+  // nx + 1 of every window row inside the domain, read while the windows load
+  if ((faces & 15) && (x0 < MSL_G || x0 + MSL_TX + MSL_G > g.nx)) {
+    constexpr int NG = NP * LR * 2 * MSL_G, NIT = (NG + 255) / 256;
+    S val[NIT];
+    int dst[NIT];   // LDS byte, -1: nothing to replace
+    int nx0 = 0, ny0 = 0;   // n0 + 1 of the nodes, two bits each
+#pragma unroll
+    for (int a = 0; a < N; ++a) {
+      nx0 |= (L.n0[0][a] + 1) << (2 * a);
+      ny0 |= (L.n0[1][a] + 1) << (2 * a);
     }
-    // ghost rows: whole padded rows in 16-byte chunks (a plane's rows share
-    // one alignment)
-    if (zgm & 12) {
-      for (int it = threadIdx.x; it < NP * 2 * MSL_G * CPR; it += 256) {
-        const int K = it / (2 * MSL_G * CPR), rem = it % (2 * MSL_G * CPR);
-        const int gr = rem / CPR, ch = rem % CPR;
-        const int side = gr / MSL_G;
-        if (!(zgm & (4 << side))) continue;
-        int wx, wy, boff;
-        origin(K, wx, wy, boff);
-        const int Y = side ? g.ny + (gr - MSL_G) : gr - MSL_G;
-        const int r = Y - wy, rs = (side ? g.ny - 1 : 0) - wy;
-        if (r < 0 || r >= LR) continue;
-        uint4 *dst = (uint4 *)(sm + K * PD + r * LWD) + ch;
-        *dst = *((const uint4 *)(sm + K * PD + rs * LWD) + ch);
+#pragma unroll
+    for (int n = 0; n < NIT; ++n) {
+      const int it = threadIdx.x + 256 * n;
+      dst[n] = -1;
+      if (it < NG) {
+        const int K = it / (LR * 2 * MSL_G), rem = it % (LR * 2 * MSL_G), row = rem >> 2, q = rem & 3;
+        const int i = K % Q, a = i % N, b = i / N;
+        const int wx = x0 + ((nx0 >> (2 * a)) & 3) - 2, X = q < 2 ? q - 2 : g.nx + q - 2, c = X - wx;
+        const int xs = mapped(0, X, g.nx), ys = mapped(1, y0 + ((ny0 >> (2 * b)) & 3) - 2 + row, g.ny);
+        if (c >= 0 && c < MSL_TX + 2 && xs >= 0 && xs < g.nx && ys >= 0 && ys < g.ny) {
+          val[n] = in[(long long)K * g.plane + g.idx(xs, ys, 0)];
+          dst[n] = (K * PD + row * LWD) * 4 + c * SZ + (int)((unsigned)((g.xo + wx) * SZ) & 3u);
+        }
       }
-      __syncthreads();
     }
+    __syncthreads();   // the compiler waits for the loads before the barrier
+#pragma unroll
+    for (int n = 0; n < NIT; ++n)
+      if (dst[n] >= 0) *(S *)((char *)sm + dst[n]) = val[n];
   }
+  __syncthreads();
 
   // reconstruction of plane K at this thread's R cells (raw storage domain)
   auto recon = [&]<int K>(C (&ft)[R]) {
