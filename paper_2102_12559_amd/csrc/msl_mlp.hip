@@ -205,20 +205,15 @@ template <int FP, int H, int OP>
 struct MlpLds {
   short w1[FP * H], w2[H * H], w3[H * OP];
   float b1[H], b2[H], b3[OP];
-  short act1[4][16 * H], act2[4][16 * H], dz2[4][16 * H], dy[4][16 * OP];
-  float red[4];
+  short act1[4][16 * H], act2[4][16 * H];
 };
 
-// mode 0: forward (Y[n][O] out); mode 1: forward + backward of the mean-square
-// loss over `inv_count` (gradient and loss partials of this workgroup)
-template <int FP, int H, int OP, int MODE>
+// forward: Y[n][O]
+template <int FP, int H, int OP>
 __global__ void __launch_bounds__(256)
 k_mlp(const float *__restrict__ prm, int F, int O, const float *__restrict__ X,
-      const float *__restrict__ Y, int n_host, const int *__restrict__ n_dev,
-      float *__restrict__ out, float *__restrict__ gpart, long long lbase, float inv_count) {
+      int n_host, const int *__restrict__ n_dev, float *__restrict__ out) {
   __shared__ MlpLds<FP, H, OP> s;
-  __shared__ float sg[MODE == 1 ? (FP * H + H + H * H + H + H * OP + OP) : 1];
-  const int P = F * H + H + H * H + H + H * O + O;
   const float *W1 = prm, *B1 = W1 + F * H, *W2 = B1 + H, *B2 = W2 + H * H, *W3 = B2 + H,
               *B3 = W3 + H * O;
   for (int k = threadIdx.x; k < FP * H; k += 256) {
@@ -232,65 +227,38 @@ k_mlp(const float *__restrict__ prm, int F, int O, const float *__restrict__ X,
   }
   for (int k = threadIdx.x; k < H; k += 256) { s.b1[k] = B1[k]; s.b2[k] = B2[k]; }
   for (int k = threadIdx.x; k < OP; k += 256) s.b3[k] = k < O ? B3[k] : 0.f;
-  if (MODE == 1)
-    for (int k = threadIdx.x; k < FP * H + H + H * H + H + H * OP + OP; k += 256) sg[k] = 0.f;
   __syncthreads();
 
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int lr = lane & 15, lg = lane >> 4;
   const int n = n_dev ? *n_dev : n_host;
   const int ntiles = (n + 15) / 16;
-  short *a1 = s.act1[w], *a2 = s.act2[w], *dz = s.dz2[w], *dyb = s.dy[w];
+  short *a1 = s.act1[w], *a2 = s.act2[w];
 
-  // gradient accumulators (mode 1)
-  f4 gw1[FP / 16][H / 16], gw2[H / 16][H / 16], gw3[H / 16][OP / 16];
-  float gb1[H / 16], gb2[H / 16], gb3[OP / 16];
-  float lossacc = 0.f;
-  if (MODE == 1) {
+  // the weight fragments stay in registers for every tile
+  s4 bw1[FP / 16][H / 16], bw2[H / 16][H / 16], bw3[H / 16][OP / 16];
 #pragma unroll
-    for (int a = 0; a < H / 16; ++a) {
-      gb1[a] = gb2[a] = 0.f;
+  for (int nt = 0; nt < H / 16; ++nt)
 #pragma unroll
-      for (int b = 0; b < FP / 16; ++b) gw1[b][a] = f4{0, 0, 0, 0};
+    for (int kc = 0; kc < FP / 16; ++kc)
 #pragma unroll
-      for (int b = 0; b < H / 16; ++b) gw2[a][b] = f4{0, 0, 0, 0};
+      for (int i = 0; i < 4; ++i) bw1[kc][nt][i] = s.w1[(kc * 16 + 4 * lg + i) * H + nt * 16 + lr];
 #pragma unroll
-      for (int b = 0; b < OP / 16; ++b) gw3[a][b] = f4{0, 0, 0, 0};
-    }
+  for (int nt = 0; nt < H / 16; ++nt)
 #pragma unroll
-    for (int b = 0; b < OP / 16; ++b) gb3[b] = 0.f;
-  }
+    for (int kc = 0; kc < H / 16; ++kc)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) bw2[kc][nt][i] = s.w2[(kc * 16 + 4 * lg + i) * H + nt * 16 + lr];
+#pragma unroll
+  for (int nt = 0; nt < OP / 16; ++nt)
+#pragma unroll
+    for (int kc = 0; kc < H / 16; ++kc)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) bw3[kc][nt][i] = s.w3[(kc * 16 + 4 * lg + i) * OP + nt * 16 + lr];
 
-  // forward only: the weight fragments stay in registers for every tile
-  s4 bw1[MODE == 0 ? FP / 16 : 1][MODE == 0 ? H / 16 : 1];
-  s4 bw2[MODE == 0 ? H / 16 : 1][MODE == 0 ? H / 16 : 1];
-  s4 bw3[MODE == 0 ? H / 16 : 1][MODE == 0 ? OP / 16 : 1];
-  if constexpr (MODE == 0) {
-#pragma unroll
-    for (int nt = 0; nt < H / 16; ++nt)
-#pragma unroll
-      for (int kc = 0; kc < FP / 16; ++kc)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) bw1[kc][nt][i] = s.w1[(kc * 16 + 4 * lg + i) * H + nt * 16 + lr];
-#pragma unroll
-    for (int nt = 0; nt < H / 16; ++nt)
-#pragma unroll
-      for (int kc = 0; kc < H / 16; ++kc)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) bw2[kc][nt][i] = s.w2[(kc * 16 + 4 * lg + i) * H + nt * 16 + lr];
-#pragma unroll
-    for (int nt = 0; nt < OP / 16; ++nt)
-#pragma unroll
-      for (int kc = 0; kc < H / 16; ++kc)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) bw3[kc][nt][i] = s.w3[(kc * 16 + 4 * lg + i) * OP + nt * 16 + lr];
-  }
-
-  const int tstride = MODE == 1 ? 1 << 30 : gridDim.x * 4;
-  for (int tile = blockIdx.x * 4 + w; tile < ntiles; tile += tstride) {
+  for (int tile = blockIdx.x * 4 + w; tile < ntiles; tile += gridDim.x * 4) {
     const int r0 = tile * 16;
     // ---- layer 1: z1 = x W1 + b1 ----
-    f4 z1[H / 16], z2[H / 16];
 #pragma unroll
     for (int nt = 0; nt < H / 16; ++nt) {
       f4 acc;
@@ -298,18 +266,15 @@ k_mlp(const float *__restrict__ prm, int F, int O, const float *__restrict__ X,
       acc = f4{bb, bb, bb, bb};
 #pragma unroll
       for (int kc = 0; kc < FP / 16; ++kc) {
-        s4 av, bv;
+        s4 av;
         const int row = r0 + lr;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int col = kc * 16 + 4 * lg + i;
           av[i] = f2bf(row < n && col < F ? X[(long long)row * F + col] : 0.f);
-          if constexpr (MODE == 0) bv[i] = bw1[kc][nt][i];
-          else bv[i] = s.w1[(kc * 16 + 4 * lg + i) * H + nt * 16 + lr];
         }
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bw1[kc][nt], acc, 0, 0, 0);
       }
-      z1[nt] = acc;
 #pragma unroll
       for (int i = 0; i < 4; ++i) a1[(4 * lg + i) * H + nt * 16 + lr] = f2bf(silu(acc[i]));
     }
@@ -322,14 +287,8 @@ k_mlp(const float *__restrict__ prm, int F, int O, const float *__restrict__ X,
 #pragma unroll
       for (int kc = 0; kc < H / 16; ++kc) {
         const s4 av = *(const s4 *)&a1[lr * H + kc * 16 + 4 * lg];
-        s4 bv;
-        if constexpr (MODE == 0) bv = bw2[kc][nt];
-        else
-#pragma unroll
-          for (int i = 0; i < 4; ++i) bv[i] = s.w2[(kc * 16 + 4 * lg + i) * H + nt * 16 + lr];
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bw2[kc][nt], acc, 0, 0, 0);
       }
-      z2[nt] = acc;
 #pragma unroll
       for (int i = 0; i < 4; ++i) a2[(4 * lg + i) * H + nt * 16 + lr] = f2bf(silu(acc[i]));
     }
@@ -343,202 +302,253 @@ k_mlp(const float *__restrict__ prm, int F, int O, const float *__restrict__ X,
 #pragma unroll
       for (int kc = 0; kc < H / 16; ++kc) {
         const s4 av = *(const s4 *)&a2[lr * H + kc * 16 + 4 * lg];
-        s4 bv;
-        if constexpr (MODE == 0) bv = bw3[kc][nt];
-        else
-#pragma unroll
-          for (int i = 0; i < 4; ++i) bv[i] = s.w3[(kc * 16 + 4 * lg + i) * OP + nt * 16 + lr];
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bw3[kc][nt], acc, 0, 0, 0);
       }
       yv[nt] = acc;
     }
-    if (MODE == 0) {
 #pragma unroll
-      for (int nt = 0; nt < OP / 16; ++nt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int row = r0 + 4 * lg + i, col = nt * 16 + lr;
-          if (row < n && col < O) out[(long long)row * O + col] = yv[nt][i];
-        }
-      continue;
-    }
-    // ---- backward ----
-    // dY = 2 (y - t) / count
-#pragma unroll
-    for (int nt = 0; nt < OP / 16; ++nt) {
-      float cs = 0.f;
+    for (int nt = 0; nt < OP / 16; ++nt)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int row = r0 + 4 * lg + i, col = nt * 16 + lr;
-        float d = 0.f;
-        if (row < n && col < O) {
-          const float e = yv[nt][i] - Y[(long long)row * O + col];
-          lossacc += e * e;
-          d = 2.f * e * inv_count;
-        }
-        dyb[(4 * lg + i) * OP + col] = f2bf(d);
-        cs += d;
+        if (row < n && col < O) out[(long long)row * O + col] = yv[nt][i];
       }
-      gb3[nt] += cs;
+  }
+}
+
+// Training: forward + backward of the mean-square loss over `inv_count`, 64
+// rows per workgroup, its gradient partial gpart[block][P] and loss partial.
+// A step has few rows (1024: 16 workgroups), so what bounds it is the length
+// of one workgroup's chain: a wave that carries 16 rows through everything by
+// itself took 41.5 us for 1024 rows of the 27 -> 64 -> 64 -> 37 network.  Here
+// H/16 waves share 16 rows, each one column tile of every layer (14.5 us).  A value
+// needed again is kept in LDS in the layout of its readers: as the rows of the
+// next product's A (R: padded so that 16 rows fall on different banks) and, as
+// the matrix core's own output layout (row = sample), as a fragment of the
+// weight gradients, whose tiles are then shared out over all waves.  Every sum
+// keeps one order: the matrix core's over k, then the workgroup's four row
+// tiles, first to last.
+template <int FP, int H, int OP>
+struct MlpTrainLds {
+  static constexpr int HT = H / 16, FT = FP / 16, OT = OP / 16, HR = H + 4, OR = OP + 4;
+  s4 f1[FT * HT * 64], f2[HT * HT * 64], f3[HT * OT * 64];   // weights, B fragments [kc][nt]
+  short w2r[H * HR], w3r[H * OR];                            // weights, rows
+  float b1[H], b2[H], b3[OP];
+  short h1r[4][16 * HR], h2r[4][16 * HR], dyr[4][16 * OR], dzr[4][16 * HR];
+  s4 xf[4][FT * 64], h1f[4][HT * 64], h2f[4][HT * 64], dyf[4][OT * 64], dz2f[4][HT * 64], dz1f[4][HT * 64];
+  float err[4][OT * 4 * 64];                                 // y - t
+  float gb1[4][H], gb2[4][H], gb3[4][OP], red[4];
+};
+
+template <int FP, int H, int OP>
+__global__ void __launch_bounds__(16 * H)
+k_mlp_train(const float *__restrict__ prm, int F, int O, const float *__restrict__ X,
+            const float *__restrict__ Y, int n, float *__restrict__ gpart, long long lbase, float inv_count) {
+  using L = MlpTrainLds<FP, H, OP>;
+  constexpr int HT = L::HT, FT = L::FT, OT = L::OT, HR = L::HR, OR = L::OR, NT = 16 * H;
+  __shared__ L s;
+  const int P = F * H + H + H * H + H + H * O + O;
+  const float *W1 = prm, *B1 = W1 + F * H, *W2 = B1 + H, *B2 = W2 + H * H, *W3 = B2 + H, *B3 = W3 + H * O;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lr = lane & 15, lg = lane >> 4;
+  const int t = wave / HT, cw = wave % HT;   // row tile, column tile
+  const int r0 = (blockIdx.x * 4 + t) * 16;
+  // this wave's inputs and targets, in flight while the weights are staged
+  float xa[FT][4], xg[4], yt[(OT + HT - 1) / HT][4];
+#pragma unroll
+  for (int kc = 0; kc < FT; ++kc)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = r0 + lr, col = kc * 16 + 4 * lg + i;
+      xa[kc][i] = row < n && col < F ? X[(long long)row * F + col] : 0.f;
     }
-    wave_sync();
-    // dW3 += h2^T dY   (M = H features, K = 16 samples, N = OP)
 #pragma unroll
-    for (int mt = 0; mt < H / 16; ++mt) {
-      s4 av;
+  for (int i = 0; i < 4; ++i) {
+    const int row = r0 + 4 * lg + i, col = cw * 16 + lr;
+    xg[i] = cw < FT && row < n && col < F ? X[(long long)row * F + col] : 0.f;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = a2[(4 * lg + i) * H + mt * 16 + lr];
-#pragma unroll
-      for (int nt = 0; nt < OP / 16; ++nt) {
-        s4 bv;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) bv[i] = dyb[(4 * lg + i) * OP + nt * 16 + lr];
-        gw3[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, gw3[mt][nt], 0, 0, 0);
-      }
-    }
-    // dH2 = dY W3^T, dZ2 = dH2 * silu'(z2)
-#pragma unroll
-    for (int nt = 0; nt < H / 16; ++nt) {
-      f4 acc = f4{0, 0, 0, 0};
-#pragma unroll
-      for (int kc = 0; kc < OP / 16; ++kc) {
-        const s4 av = *(const s4 *)&dyb[lr * OP + kc * 16 + 4 * lg];
-        const s4 bv = *(const s4 *)&s.w3[(nt * 16 + lr) * OP + kc * 16 + 4 * lg];
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, acc, 0, 0, 0);
-      }
-      float cs = 0.f;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float d = acc[i] * silu_d(z2[nt][i]);
-        dz[(4 * lg + i) * H + nt * 16 + lr] = f2bf(d);
-        cs += d;
-      }
-      gb2[nt] += cs;
-    }
-    wave_sync();
-    // dW2 += h1^T dZ2
-#pragma unroll
-    for (int mt = 0; mt < H / 16; ++mt) {
-      s4 av;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = a1[(4 * lg + i) * H + mt * 16 + lr];
-#pragma unroll
-      for (int nt = 0; nt < H / 16; ++nt) {
-        s4 bv;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) bv[i] = dz[(4 * lg + i) * H + nt * 16 + lr];
-        gw2[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, gw2[mt][nt], 0, 0, 0);
-      }
-    }
-    // dH1 = dZ2 W2^T, dZ1 = dH1 * silu'(z1)   (kept in act2, no longer needed)
-#pragma unroll
-    for (int nt = 0; nt < H / 16; ++nt) {
-      f4 acc = f4{0, 0, 0, 0};
-#pragma unroll
-      for (int kc = 0; kc < H / 16; ++kc) {
-        const s4 av = *(const s4 *)&dz[lr * H + kc * 16 + 4 * lg];
-        const s4 bv = *(const s4 *)&s.w2[(nt * 16 + lr) * H + kc * 16 + 4 * lg];
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, acc, 0, 0, 0);
-      }
-      float cs = 0.f;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float d = acc[i] * silu_d(z1[nt][i]);
-        a2[(4 * lg + i) * H + nt * 16 + lr] = f2bf(d);
-        cs += d;
-      }
-      gb1[nt] += cs;
-    }
-    wave_sync();
-    // dW1 += x^T dZ1
-#pragma unroll
-    for (int mt = 0; mt < FP / 16; ++mt) {
-      s4 av;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = r0 + 4 * lg + i, col = mt * 16 + lr;
-        av[i] = f2bf(row < n && col < F ? X[(long long)row * F + col] : 0.f);
-      }
-#pragma unroll
-      for (int nt = 0; nt < H / 16; ++nt) {
-        s4 bv;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) bv[i] = a2[(4 * lg + i) * H + nt * 16 + lr];
-        gw1[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, gw1[mt][nt], 0, 0, 0);
-      }
+    for (int k = 0; k < (OT + HT - 1) / HT; ++k) {
+      const int o = (cw + k * HT) * 16 + lr;
+      yt[k][i] = row < n && o < O ? Y[(long long)row * O + o] : 0.f;
     }
   }
-  if (MODE != 1) return;
-  // ---- deterministic workgroup reduction: waves add in order ----
-  // bias sums: combine the four lane groups of each column
+  // element (k, c) of a weight matrix in its B fragment [k / 16][c / 16]
+  auto frag = [](s4 *fr, int nct, int k, int c) -> short & {
+    return ((short *)fr)[(((k / 16) * nct + c / 16) * 64 + ((k % 16) / 4) * 16 + c % 16) * 4 + k % 4];
+  };
 #pragma unroll
-  for (int a = 0; a < H / 16; ++a) {
-    gb1[a] += __shfl_xor(gb1[a], 16);
-    gb1[a] += __shfl_xor(gb1[a], 32);
-    gb2[a] += __shfl_xor(gb2[a], 16);
-    gb2[a] += __shfl_xor(gb2[a], 32);
+  for (int k0 = 0; k0 < FP * H; k0 += NT) {
+    const int k = k0 + threadIdx.x, f = k / H;
+    if (k < FP * H) frag(s.f1, HT, f, k % H) = f2bf(f < F ? W1[k] : 0.f);
   }
 #pragma unroll
-  for (int a = 0; a < OP / 16; ++a) {
-    gb3[a] += __shfl_xor(gb3[a], 16);
-    gb3[a] += __shfl_xor(gb3[a], 32);
+  for (int k0 = 0; k0 < H * H; k0 += NT) {
+    const int k = k0 + threadIdx.x;
+    const short v = f2bf(W2[k]);
+    frag(s.f2, HT, k / H, k % H) = v;
+    s.w2r[(k / H) * HR + k % H] = v;
   }
-  for (int m = 1; m < 64; m <<= 1) lossacc += __shfl_xor(lossacc, m);
-  const int oW1 = 0, oB1 = FP * H, oW2 = oB1 + H, oB2 = oW2 + H * H, oW3 = oB2 + H,
-            oB3 = oW3 + H * OP;
-  for (int wv = 0; wv < 4; ++wv) {
-    if (w == wv) {
 #pragma unroll
-      for (int mt = 0; mt < FP / 16; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < H / 16; ++nt)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            sg[oW1 + (mt * 16 + 4 * lg + i) * H + nt * 16 + lr] += gw1[mt][nt][i];
-#pragma unroll
-      for (int mt = 0; mt < H / 16; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < H / 16; ++nt)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            sg[oW2 + (mt * 16 + 4 * lg + i) * H + nt * 16 + lr] += gw2[mt][nt][i];
-#pragma unroll
-      for (int mt = 0; mt < H / 16; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < OP / 16; ++nt)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            sg[oW3 + (mt * 16 + 4 * lg + i) * OP + nt * 16 + lr] += gw3[mt][nt][i];
-      if (lg == 0) {
-#pragma unroll
-        for (int a = 0; a < H / 16; ++a) {
-          sg[oB1 + a * 16 + lr] += gb1[a];
-          sg[oB2 + a * 16 + lr] += gb2[a];
-        }
-#pragma unroll
-        for (int a = 0; a < OP / 16; ++a) sg[oB3 + a * 16 + lr] += gb3[a];
-      }
-      if (lane == 0) s.red[wv] = lossacc;
+  for (int k0 = 0; k0 < H * OP; k0 += NT) {
+    const int k = k0 + threadIdx.x, h = k / OP, o = k % OP;
+    if (k < H * OP) {
+      const short v = f2bf(o < O ? W3[h * O + o] : 0.f);
+      frag(s.f3, OT, h, o) = v;
+      s.w3r[h * OR + o] = v;
     }
-    __syncthreads();
   }
-  // unpadded layout of this workgroup's partial
+  if (threadIdx.x < H) {
+    s.b1[threadIdx.x] = B1[threadIdx.x];
+    s.b2[threadIdx.x] = B2[threadIdx.x];
+  }
+  if (threadIdx.x < OP) s.b3[threadIdx.x] = threadIdx.x < O ? B3[threadIdx.x] : 0.f;
+  if (cw < FT) s.xf[t][cw * 64 + lane] = s4{f2bf(xg[0]), f2bf(xg[1]), f2bf(xg[2]), f2bf(xg[3])};
+  __syncthreads();
+  const int c = cw * 16 + lr;   // this lane's column
+  // ---- forward ----
+  auto layer = [&](int kct, auto av, const s4 *wf, int nct, int nt, float bb) {
+    f4 acc = f4{bb, bb, bb, bb};
+#pragma unroll
+    for (int kc = 0; kc < kct; ++kc)
+      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av(kc), wf[(kc * nct + nt) * 64 + lane], acc, 0, 0, 0);
+    return acc;
+  };
+  auto rows = [&](const short *a, int stride) {   // A fragments of a product over a's columns
+    return [=](int kc) { return *(const s4 *)&a[lr * stride + kc * 16 + 4 * lg]; };
+  };
+  auto keep = [&](short *r, int stride, s4 *fr, int nt, const float (&v)[4]) {
+    const s4 q = s4{f2bf(v[0]), f2bf(v[1]), f2bf(v[2]), f2bf(v[3])};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[(4 * lg + i) * stride + nt * 16 + lr] = q[i];
+    fr[nt * 64 + lane] = q;
+  };
+  const f4 z1 = layer(FT, [&](int kc) { return s4{f2bf(xa[kc][0]), f2bf(xa[kc][1]), f2bf(xa[kc][2]), f2bf(xa[kc][3])}; },
+                      s.f1, HT, cw, s.b1[c]);
+  {
+    const float h[4] = {silu(z1[0]), silu(z1[1]), silu(z1[2]), silu(z1[3])};
+    keep(s.h1r[t], HR, s.h1f[t], cw, h);
+  }
+  __syncthreads();
+  const f4 z2 = layer(HT, rows(s.h1r[t], HR), s.f2, HT, cw, s.b2[c]);
+  {
+    const float h[4] = {silu(z2[0]), silu(z2[1]), silu(z2[2]), silu(z2[3])};
+    keep(s.h2r[t], HR, s.h2f[t], cw, h);
+  }
+  __syncthreads();
+  // bias gradients: a column's sum over the rows of the tile
+  auto colsum = [&](float *gb, int col, float cs) {
+    cs = 0.f + cs;
+    cs += __shfl_xor(cs, 16);
+    cs += __shfl_xor(cs, 32);
+    if (lg == 0) gb[col] = cs;
+  };
+  // output and dY = 2 (y - t) / count
+#pragma unroll
+  for (int k = 0; k < (OT + HT - 1) / HT; ++k) {
+    const int nt = cw + k * HT;
+    if (nt >= OT) break;
+    const f4 y = layer(HT, rows(s.h2r[t], HR), s.f3, OT, nt, s.b3[nt * 16 + lr]);
+    float cs = 0.f, d[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = r0 + 4 * lg + i, col = nt * 16 + lr;
+      float e = 0.f;
+      d[i] = 0.f;
+      if (row < n && col < O) {
+        e = y[i] - yt[k][i];
+        d[i] = 2.f * e * inv_count;
+      }
+      s.err[t][(nt * 4 + i) * 64 + lane] = e;
+      cs += d[i];
+    }
+    keep(s.dyr[t], OR, s.dyf[t], nt, d);
+    colsum(s.gb3[t], nt * 16 + lr, cs);
+  }
+  __syncthreads();
+  // ---- backward ----
+  // dH2 = dY W3^T, dZ2 = dH2 * silu'(z2); dH1 = dZ2 W2^T, dZ1 = dH1 * silu'(z1)
+  {
+    f4 acc = f4{0, 0, 0, 0};
+#pragma unroll
+    for (int kc = 0; kc < OT; ++kc)
+      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(rows(s.dyr[t], OR)(kc), *(const s4 *)&s.w3r[c * OR + kc * 16 + 4 * lg],
+                                                      acc, 0, 0, 0);
+    float cs = 0.f, d[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      d[i] = acc[i] * silu_d(z2[i]);
+      cs += d[i];
+    }
+    keep(s.dzr[t], HR, s.dz2f[t], cw, d);
+    colsum(s.gb2[t], c, cs);
+  }
+  __syncthreads();
+  {
+    f4 acc = f4{0, 0, 0, 0};
+#pragma unroll
+    for (int kc = 0; kc < HT; ++kc)
+      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(rows(s.dzr[t], HR)(kc), *(const s4 *)&s.w2r[c * HR + kc * 16 + 4 * lg],
+                                                      acc, 0, 0, 0);
+    float cs = 0.f, d[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      d[i] = acc[i] * silu_d(z1[i]);
+      cs += d[i];
+    }
+    s.dz1f[t][cw * 64 + lane] = s4{f2bf(d[0]), f2bf(d[1]), f2bf(d[2]), f2bf(d[3])};
+    colsum(s.gb1[t], c, cs);
+  }
+  // loss of the tile, its errors in ascending column tile
+  if (cw == HT - 1) {
+    float l = 0.f;
+#pragma unroll
+    for (int k = 0; k < OT * 4; ++k) {
+      const float e = s.err[t][k * 64 + lane];
+      l += e * e;
+    }
+    for (int m = 1; m < 64; m <<= 1) l += __shfl_xor(l, m);
+    if (lane == 0) s.red[t] = l;
+  }
+  __syncthreads();
+  // ---- weight gradients: x^T dZ1, h1^T dZ2, h2^T dY over the live row tiles ----
+  const int live = min(4, (n - (int)blockIdx.x * 64 + 15) / 16);
   float *gp = gpart + (long long)blockIdx.x * P;
-  for (int k = threadIdx.x; k < P; k += 256) {
-    float v;
-    if (k < F * H) v = sg[oW1 + (k / H) * H + k % H];
-    else if (k < F * H + H) v = sg[oB1 + (k - F * H)];
-    else if (k < F * H + H + H * H) v = sg[oW2 + (k - F * H - H)];
-    else if (k < F * H + 2 * H + H * H) v = sg[oB2 + (k - F * H - H - H * H)];
-    else if (k < F * H + 2 * H + H * H + H * O) {
-      const int r = k - (F * H + 2 * H + H * H);
-      v = sg[oW3 + (r / O) * OP + r % O];
-    } else {
-      v = sg[oB3 + (k - (F * H + 2 * H + H * H + H * O))];
+  constexpr int G1 = FT * HT, G2 = G1 + HT * HT, G3 = G2 + HT * OT;
+  for (int k = wave; k < G3; k += 4 * HT) {
+    // A and B fragments, their strides between row tiles; rows, columns and
+    // place of the gradient matrix
+    const int q = k < G1 ? k : (k < G2 ? k - G1 : k - G2), nct = k < G2 ? HT : OT, mt = q / nct, nt = q % nct;
+    const s4 *A = (k < G1 ? s.xf[0] : (k < G2 ? s.h1f[0] : s.h2f[0])) + mt * 64 + lane;
+    const s4 *B = (k < G1 ? s.dz1f[0] : (k < G2 ? s.dz2f[0] : s.dyf[0])) + nt * 64 + lane;
+    const int as = (k < G1 ? FT : HT) * 64, bs = nct * 64;
+    f4 g = f4{0, 0, 0, 0};
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (u < live) {
+        const f4 p = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(A[u * as], B[u * bs], f4{0, 0, 0, 0}, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) g[i] += p[i];
+      }
+    const int rows_n = k < G1 ? F : H, cols = k < G2 ? H : O, col = nt * 16 + lr;
+    float *dst = gp + (k < G1 ? 0 : (k < G2 ? F * H + H : F * H + 2 * H + H * H));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = mt * 16 + 4 * lg + i;
+      if (row < rows_n && col < cols) dst[row * cols + col] = g[i];
     }
-    gp[k] = v;
   }
-  if (threadIdx.x == 0) gpart[lbase + blockIdx.x] = s.red[0] + s.red[1] + s.red[2] + s.red[3];
+  const int th = threadIdx.x;
+  auto tiles = [&](const float *gb, int stride) {
+    float v = 0.f;
+    for (int u = 0; u < 4; ++u) v += gb[u * stride];
+    return v;
+  };
+  if (th < H) {
+    gp[F * H + th] = tiles(&s.gb1[0][th], H);
+    gp[F * H + H + H * H + th] = tiles(&s.gb2[0][th], H);
+  }
+  if (th < O) gp[F * H + 2 * H + H * H + H * O + th] = tiles(&s.gb3[0][th], OP);
+  if (th == 0) gpart[lbase + blockIdx.x] = s.red[0] + s.red[1] + s.red[2] + s.red[3];
 }
 
 // sum of the workgroup partials in a fixed order; optionally Adam
@@ -548,14 +558,23 @@ __global__ void k_mlp_reduce_adam(float *__restrict__ prm, float *__restrict__ m
                                   int apply, int t, float lr, float b1, float b2, float eps,
                                   float *__restrict__ loss_out, float loss_scale) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k == 0 && loss_out) {
-    float L = 0.f;
-    for (int b = 0; b < nblk; ++b) L += gpart[lbase + b];
-    *loss_out = L * loss_scale;
-  }
+  // first to last, 16 loads in flight (one after the other they were most of
+  // the 6.6 us that the sums over 16 workgroups took; now 4.0 us, a launch of this size 2 to 3)
+  auto sum = [&](const float *p, long long stride) {
+    float a = 0.f;
+    for (int b0 = 0; b0 < nblk; b0 += 16) {
+      float q[16];
+#pragma unroll
+      for (int b = 0; b < 16; ++b) q[b] = b0 + b < nblk ? p[(b0 + b) * stride] : 0.f;
+#pragma unroll
+      for (int b = 0; b < 16; ++b)
+        if (b0 + b < nblk) a += q[b];
+    }
+    return a;
+  };
+  if (k == 0 && loss_out) *loss_out = sum(gpart + lbase, 1) * loss_scale;
   if (k >= P) return;
-  float g = 0.f;
-  for (int b = 0; b < nblk; ++b) g += gpart[(long long)b * P + k];
+  const float g = sum(gpart + k, P);
   if (gout) gout[k] = g;
   if (!apply) return;
   const float mk = b1 * m[k] + (1.f - b1) * g;
@@ -987,25 +1006,12 @@ k_snapshots(const Tab *__restrict__ tab, Geo g, const char *bh, long long nmax,
 // ---------------------------------------------------------------------------
 static inline int lerr() { return hipGetLastError() == hipSuccess ? MSL_OK : MSL_EHIP; }
 
-// gpart: gradient partials [nblk][P] followed, at lbase, by the loss partials
-// (nullptr: the workspace's, laid out for MSL_MLP_MAXBLK workgroups)
-template <int MODE>
-static int mlp_launch(msl_ctx *c, const float *X, const float *Y, int n, const int *n_dev,
-                      float *out, float inv_count, int nblk, float *gpart = nullptr,
-                      long long lbase = -1) {
-  const int F = c->mlpF, O = c->mlpO, H = c->mlpH;
-  const int FPd = (F + 15) / 16 * 16, OPd = (O + 15) / 16 * 16;
-  const dim3 grid(nblk), block(256);
-  if (!gpart) {
-    gpart = c->mlp_gpart;
-    lbase = (long long)MSL_MLP_MAXBLK * c->mlpP;
-  }
-#define MLP_CASE(FPv, Hv, OPv)                                                                    \
-  if (FPd == FPv && H == Hv && OPd == OPv) {                                                      \
-    hipLaunchKernelGGL((k_mlp<FPv, Hv, OPv, MODE>), grid, block, 0, c->stream, c->mlp_w, F, O, X, \
-                       Y, n, n_dev, out, gpart, lbase, inv_count);                                \
-    return lerr();                                                                                \
-  }
+// the network's padded sizes, as a compile-time case
+template <typename Fn>
+static int mlp_sizes(msl_ctx *c, Fn &&f) {
+  const int FP = (c->mlpF + 15) / 16 * 16, OP = (c->mlpO + 15) / 16 * 16, H = c->mlpH;
+#define MLP_CASE(FPv, Hv, OPv) \
+  if (FP == FPv && H == Hv && OP == OPv) return f.template operator()<FPv, Hv, OPv>();
   MLP_CASE(16, 64, 16)
   MLP_CASE(16, 64, 32)
   MLP_CASE(16, 64, 48)
@@ -1016,6 +1022,14 @@ static int mlp_launch(msl_ctx *c, const float *X, const float *Y, int n, const i
   MLP_CASE(32, 32, 48)
 #undef MLP_CASE
   return MSL_EINVAL;
+}
+
+static int mlp_forward(msl_ctx *c, const float *X, int n, const int *n_dev, float *out, int nblk) {
+  return mlp_sizes(c, [&]<int FP, int H, int OP>() {
+    hipLaunchKernelGGL((k_mlp<FP, H, OP>), dim3(nblk), dim3(256), 0, c->stream, c->mlp_w, c->mlpF, c->mlpO, X, n,
+                       n_dev, out);
+    return lerr();
+  });
 }
 
 template <typename F>
@@ -1049,7 +1063,7 @@ int msl_mlp_band_lift(msl_ctx *c, char *bl, char *bh) {
   if (rc) return rc;
   // 768 workgroups: three per CU, as many as its LDS (50 KB each) and
   // registers hold (measured 6 % faster than two per CU on the 3D band)
-  rc = mlp_launch<0>(c, c->mlp_feat, nullptr, 0, c->bcount, c->mlp_out, 0.f, 768);
+  rc = mlp_forward(c, c->mlp_feat, 0, c->bcount, c->mlp_out, 768);
   if (rc) return rc;
   return store_dispatch(c->cfg.store, [&]<typename S>() {
     return msl_pair_dispatch(c->D, c->htab.lat[0].n, c->htab.lat[1].n, [&]<int D, int NL, int NH>() {
@@ -1084,7 +1098,7 @@ int msl_mlp_check_launch(msl_ctx *c) {
     });
   });
   if (rc) return rc;
-  rc = mlp_launch<0>(c, c->mlp_feat, nullptr, 0, c->bcount + 1, c->mlp_out, 0.f, 768);
+  rc = mlp_forward(c, c->mlp_feat, 0, c->bcount + 1, c->mlp_out, 768);
   if (rc) return rc;
   hipLaunchKernelGGL(k_check_cells, dim3(512), dim3(256), 0, c->stream, c->bcount + 1,
                      c->mlp_stats, c->mlpF, c->mlpO, c->mlp_out, c->mlp_tgt, c->mlp_cerr);
@@ -1188,7 +1202,7 @@ int msl_mlp_get_weights(msl_ctx *c, float *params) {
 
 int msl_mlp_forward(msl_ctx *c, const float *X, int n, float *Yout) {
   if (!c || !X || !Yout || n < 0 || !c->mlpP) return MSL_EINVAL;
-  int rc = mlp_launch<0>(c, X, nullptr, n, nullptr, Yout, 0.f, 256);
+  int rc = mlp_forward(c, X, n, nullptr, Yout, 256);
   if (rc) return rc;
   MSL_HIP(hipStreamSynchronize(c->stream));
   return MSL_OK;
@@ -1203,7 +1217,11 @@ static int grad_step(msl_ctx *c, const float *X, const float *Y, int n, int appl
     lbase = (long long)MSL_MLP_MAXBLK * c->mlpP;
   }
   const float invc = 1.f / ((float)n * (float)c->mlpO);
-  int rc = mlp_launch<1>(c, X, Y, n, nullptr, nullptr, invc, nblk, gpart, lbase);
+  int rc = mlp_sizes(c, [&]<int FP, int H, int OP>() {
+    hipLaunchKernelGGL((k_mlp_train<FP, H, OP>), dim3(nblk), dim3(16 * H), 0, c->stream, c->mlp_w, c->mlpF, c->mlpO,
+                       X, Y, n, gpart, lbase, invc);
+    return lerr();
+  });
   if (rc) return rc;
   const int t = apply ? (int)(++c->mlp_steps) : 1;
   hipLaunchKernelGGL(k_mlp_reduce_adam, dim3((c->mlpP + 255) / 256), dim3(256), 0, c->stream,
