@@ -818,7 +818,7 @@ static bool crit_step(const msl_ctx *c, long step) {
 
 // the launches of one step after its criterion pass: ghost fill,
 // stream-collide of each set, band conversion (and the learned lift).  fork
-// (only while capturing): the high-order set's stream-collide launch goes on
+// (only while capturing, sets launched apart): the high-order set's launch goes on
 // a parallel branch, forked after the ghost fill and joined before the band
 // conversion
 // 3D with x periodic on both faces: the x ghosts are kept current by the
@@ -839,7 +839,14 @@ static int plain_step(msl_ctx *c, bool fork) {
   rc = msl_launch_bc(c, bl, bh);
   if (rc) { set_err(c, "ghost fill failed"); return rc; }
   if ((rc = prof_end(c, 0, -1, 0.0, 0.0))) return rc;
-  fork = fork && c->nlat > 1;
+  // small 2D grids: both sets in one launch (timed launches stay apart)
+  bool paired = false;
+  if (c->fuse && !prof_on(c)) {
+    rc = msl_launch_stream_pair(c, cur);
+    if (rc != MSL_OK && rc != MSL_ESTATE) { set_err(c, "stream-collide launch failed"); return rc; }
+    paired = rc == MSL_OK;
+  }
+  fork = fork && c->nlat > 1 && !paired;
   if (fork) {
     hipStream_t s0 = c->stream;
     MSL_HIP(hipEventRecord(c->gev[0], s0));
@@ -856,7 +863,7 @@ static int plain_step(msl_ctx *c, bool fork) {
       return rc;
     }
   }
-  for (int l = 0; l < (fork ? 1 : c->nlat); ++l) {
+  for (int l = 0; l < (paired ? 0 : fork ? 1 : c->nlat); ++l) {
     // compulsory traffic: read and write every population plane of each native cell
     const double bpc = 2.0 * c->Q[l] * (c->cfg.thermal ? 2 : 1) * (double)c->esz;
     prof_begin(c);

@@ -224,6 +224,7 @@ struct msl_ctx {
 // oth: the other set's new planes, written at this set's band cells (2D
 // two-set contexts where msl_stream_sc2_all holds); nullptr: no conversion
 int msl_launch_stream_collide(msl_ctx *c, int lat, const char *in, char *out, char *oth);
+int msl_launch_stream_pair(msl_ctx *c, int cur);
 // every set of a 2D context runs the stream-collide kernel with all planes
 // resident in LDS
 int msl_stream_sc2_all(const msl_ctx *c);

@@ -5,6 +5,8 @@ template <typename S, bool TH>
 int msl_launch_store_th(msl_ctx *c, int lat, const char *in, char *out, char *oth);
 template <typename S, bool TH>
 int msl_sc2_all_th(const msl_ctx *c);
+template <typename S, bool TH>
+int msl_launch_pair_th(msl_ctx *c, int cur);
 
 template <typename S>
 static int store_s(msl_ctx *c, int lat, const char *in, char *out, char *oth) {
@@ -35,4 +37,19 @@ int msl_stream_sc2_all(const msl_ctx *c) {
     case MSL_BF16_DEV: return sc2_all_s<bf16_t>(c);
   }
   return 0;
+}
+
+template <typename S>
+static int pair_s(msl_ctx *c, int cur) {
+  return c->cfg.thermal ? msl_launch_pair_th<S, true>(c, cur) : msl_launch_pair_th<S, false>(c, cur);
+}
+
+int msl_launch_stream_pair(msl_ctx *c, int cur) {
+  switch (c->cfg.store) {
+    case MSL_FP64: return pair_s<double>(c, cur);
+    case MSL_FP32: return pair_s<float>(c, cur);
+    case MSL_FP16_DEV: return pair_s<_Float16>(c, cur);
+    case MSL_BF16_DEV: return pair_s<bf16_t>(c, cur);
+  }
+  return MSL_EINVAL;
 }

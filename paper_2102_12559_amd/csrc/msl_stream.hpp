@@ -237,6 +237,45 @@ int msl_launch_store_th(msl_ctx *c, int lat, const char *in, char *out, char *ot
   return launch_n<S, TH>(c, lat, in, out, oth);
 }
 
+// both sets of a fused 2D run in one launch; MSL_ESTATE: not for this grid (the
+// caller launches them one after the other).  The line, 8 workgroups per CU of
+// both sets' tiles: us per step with a sixteenth of the grid high-order, one
+// launch against two: FP64 D2Q9+D2Q16 64^2 6.4, 12.8, 256^2 7.3, 12.2, 512^2
+// (1536 workgroups) 16.4, 19.2; FP32 D2Q9+D2Q36 64^2 9.9, 17.7, 512^2 17.0,
+// 19.7, but 768^2 (3456) 26.9, 25.2 and 1024^2 51.1, 33.1 (in one launch the
+// low-order tiles hold the other set's LDS).
+template <typename S, bool TH, int NL, int NH>
+static int launch_pair(msl_ctx *c, int cur) {
+  using P = SC2PairTraits<S, TH, NL, NH>;
+  if constexpr (P::fits) {
+    const Geo &g = c->geo;
+    const long long nlo = (long long)g.ntx * ((g.ny + P::TL::TY - 1) / P::TL::TY);
+    const long long nhi = (long long)g.ntx * ((g.ny + P::TH_::TY - 1) / P::TH_::TY);
+    if (nlo + nhi > 2048) return MSL_ESTATE;
+    auto run = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)(nlo + nhi)), dim3(256), 0, c->stream, c->dtab, g,
+                         (const S *)c->planes[0][cur], (S *)c->planes[0][cur ^ 1], (const S *)c->planes[1][cur],
+                         (S *)c->planes[1][cur ^ 1], c->cls, c->tflag, (int)nlo, c->faces);
+    };
+    if (c->htab.qe) run(k_sc2d_pair<S, TH, NL, NH, true>);
+    else run(k_sc2d_pair<S, TH, NL, NH, false>);
+    return hipGetLastError() == hipSuccess ? MSL_OK : MSL_EHIP;
+  }
+  return MSL_ESTATE;
+}
+
+template <typename S, bool TH>
+int msl_launch_pair_th(msl_ctx *c, int cur) {
+  const int nl = c->htab.lat[0].n, nh = c->htab.lat[1].n;
+  if (nl == 3 && nh == 4) return launch_pair<S, TH, 3, 4>(c, cur);
+  if (nl == 3 && nh == 5) return launch_pair<S, TH, 3, 5>(c, cur);
+  if (nl == 3 && nh == 6) return launch_pair<S, TH, 3, 6>(c, cur);
+  if (nl == 4 && nh == 5) return launch_pair<S, TH, 4, 5>(c, cur);
+  if (nl == 4 && nh == 6) return launch_pair<S, TH, 4, 6>(c, cur);
+  if (nl == 5 && nh == 6) return launch_pair<S, TH, 5, 6>(c, cur);
+  return MSL_ESTATE;
+}
+
 // every set of a 2D context runs the kernel with all planes resident in LDS
 // (which can convert band cells itself)
 template <typename S, bool TH>

@@ -110,25 +110,31 @@ __device__ __forceinline__ V msl_lane_get(V v, int lane) {
 // set, in the new buffer `oth` of the other set's planes: the low-order
 // launch lifts (NO > N), the high-order launch projects (NO < N), each from
 // the post-collision populations it holds in registers.
-template <typename S, bool TH, int N, bool SMALL, bool LIST = false, bool QE = false, int NO = 0>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SC2Traits<S, TH, N, SMALL>::WAVES)))
-k_sc2d_res(const Tab *__restrict__ tab, int lat, Geo g, const S *__restrict__ in,
-           S *__restrict__ out, const uint8_t *__restrict__ cls,
-           const uint8_t *__restrict__ tflag, int remap, int nt, const int *__restrict__ tlist,
-           const int *__restrict__ tcount, S *__restrict__ oth, int faces) {
+// LDS of a launch: every plane's window, and the conversion tables
+template <typename S, bool TH, int N, bool SMALL, int NO>
+struct SC2Lds {
+  using Tr = SC2Traits<S, TH, N, SMALL>;
+  static constexpr bool LIFT = NO > N, PROJ = NO > 0 && NO < N;
+  static constexpr int SM = Tr::NP * Tr::PD;
+  static constexpr int NTAB = LIFT ? NO * NO + 2 * NO * N + NO * NO : (PROJ ? NO * N + NO * NO : 1);
+};
+
+// tile (bx, by) of set `lat`
+template <typename S, bool TH, int N, bool SMALL, bool QE, int NO>
+__device__ __forceinline__ void sc2d_tile(const Tab *__restrict__ tab, int lat, const Geo &g, const S *__restrict__ in,
+                                          S *__restrict__ out, const uint8_t *__restrict__ cls,
+                                          const uint8_t *__restrict__ tflag, int nt, S *__restrict__ oth, int faces,
+                                          uint32_t *sm, double *stab, const int bx, const int by) {
   using Tr = SC2Traits<S, TH, N, SMALL>;
   using T = typename Tr::T;
   using C = typename Tr::C;
   constexpr int Q = Tr::Q, NP = Tr::NP, R = Tr::R, TY = Tr::TY, PD = Tr::PD, M = Tr::M;
   constexpr int LWD = Tr::LWD, SZ = Tr::SZ;
   constexpr int LR = TY + 2;
-  __shared__ uint32_t sm[NP * PD];
-  constexpr bool LIFT = NO > N, PROJ = NO > 0 && NO < N;
+  constexpr bool LIFT = SC2Lds<S, TH, N, SMALL, NO>::LIFT, PROJ = SC2Lds<S, TH, N, SMALL, NO>::PROJ;
   constexpr int QO = NO * NO;
-  constexpr int NTAB = LIFT ? NO * NO + 2 * NO * N + QO : (PROJ ? NO * N + QO : 1);
-  __shared__ double stab[NTAB];
+  constexpr int NTAB = SC2Lds<S, TH, N, SMALL, NO>::NTAB;
   const LatTab &L = tab->lat[lat];
-  auto tile_body = [&](const int bx, const int by) {
   const int x0 = bx * MSL_TX, y0 = by * TY;
   {
     uint8_t any = 0;
@@ -680,6 +686,19 @@ k_sc2d_res(const Tab *__restrict__ tab, int lat, Geo g, const S *__restrict__ in
       }
     }
   }
+}
+
+template <typename S, bool TH, int N, bool SMALL, bool LIST = false, bool QE = false, int NO = 0>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SC2Traits<S, TH, N, SMALL>::WAVES)))
+k_sc2d_res(const Tab *__restrict__ tab, int lat, Geo g, const S *__restrict__ in,
+           S *__restrict__ out, const uint8_t *__restrict__ cls,
+           const uint8_t *__restrict__ tflag, int remap, int nt, const int *__restrict__ tlist,
+           const int *__restrict__ tcount, S *__restrict__ oth, int faces) {
+  using Lds = SC2Lds<S, TH, N, SMALL, NO>;
+  __shared__ uint32_t sm[Lds::SM];
+  __shared__ double stab[Lds::NTAB];
+  auto tile_body = [&](int bx, int by) {
+    sc2d_tile<S, TH, N, SMALL, QE, NO>(tab, lat, g, in, out, cls, tflag, nt, oth, faces, sm, stab, bx, by);
   };
   if constexpr (LIST) {
     // sparse launch: one workgroup per entry of the compact list of live
@@ -699,4 +718,37 @@ k_sc2d_res(const Tab *__restrict__ tab, int lat, Geo g, const S *__restrict__ in
     const int tile = remap ? msl_xcd_tile(lin, (int)(gridDim.x * gridDim.y)) : lin;
     tile_body(tile % (int)gridDim.x, tile / (int)gridDim.x);
   }
+}
+
+// Both sets of a fused two-set run in one launch, on small grids: there a launch
+// is as long as a workgroup's chain or two (6.9 us each for D2Q9 and D2Q16 on
+// 64^2), the sets' tiles write different cells, and one launch after the other
+// pays that twice.  nlo: tiles of the low-order set.
+template <typename S, bool TH, int NL, int NH>
+struct SC2PairTraits {
+  static constexpr bool SMALL = NL == 3;   // 4-row D2Q9 tiles
+  using TL = SC2Traits<S, TH, NL, SMALL>;
+  using TH_ = SC2Traits<S, TH, NH>;
+  static constexpr bool fits = TL::fits && TH_::fits;
+  // register budget: the tighter occupancy target of the two
+  static constexpr int WAVES = TL::WAVES < TH_::WAVES ? TL::WAVES : TH_::WAVES;
+};
+
+template <typename S, bool TH, int NL, int NH, bool QE>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SC2PairTraits<S, TH, NL, NH>::WAVES)))
+k_sc2d_pair(const Tab *__restrict__ tab, Geo g, const S *__restrict__ in_l, S *__restrict__ out_l,
+            const S *__restrict__ in_h, S *__restrict__ out_h, const uint8_t *__restrict__ cls,
+            const uint8_t *__restrict__ tflag, int nlo, int faces) {
+  using P = SC2PairTraits<S, TH, NL, NH>;
+  using LL = SC2Lds<S, TH, NL, P::SMALL, NH>;
+  using LH = SC2Lds<S, TH, NH, false, NL>;
+  __shared__ uint32_t sm[LL::SM > LH::SM ? LL::SM : LH::SM];
+  __shared__ double stab[LL::NTAB > LH::NTAB ? LL::NTAB : LH::NTAB];
+  const int lin = (int)blockIdx.x;
+  if (lin < nlo)
+    sc2d_tile<S, TH, NL, P::SMALL, QE, NH>(tab, 0, g, in_l, out_l, cls, tflag, 0, out_h, faces, sm, stab, lin % g.ntx,
+                                           lin / g.ntx);
+  else
+    sc2d_tile<S, TH, NH, false, QE, NL>(tab, 1, g, in_h, out_h, cls, tflag, 0, out_l, faces, sm, stab,
+                                        (lin - nlo) % g.ntx, (lin - nlo) / g.ntx);
 }
