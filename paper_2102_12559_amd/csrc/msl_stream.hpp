@@ -238,12 +238,13 @@ int msl_launch_store_th(msl_ctx *c, int lat, const char *in, char *out, char *ot
 }
 
 // both sets of a fused 2D run in one launch; MSL_ESTATE: not for this grid (the
-// caller launches them one after the other).  The line, 8 workgroups per CU of
-// both sets' tiles: us per step with a sixteenth of the grid high-order, one
-// launch against two: FP64 D2Q9+D2Q16 64^2 6.4, 12.8, 256^2 7.3, 12.2, 512^2
-// (1536 workgroups) 16.4, 19.2; FP32 D2Q9+D2Q36 64^2 9.9, 17.7, 512^2 17.0,
-// 19.7, but 768^2 (3456) 26.9, 25.2 and 1024^2 51.1, 33.1 (in one launch the
-// low-order tiles hold the other set's LDS).
+// caller launches them one after the other).  The line: what the CUs hold by the
+// launch's LDS four times over, at most 8 workgroups per CU.  us per step with a
+// sixteenth of the grid high-order, one launch against two: FP64 D2Q9+D2Q16 64^2
+// 6.4, 12.8, 256^2 7.3, 12.2, 512^2 (1536 workgroups) 16.4, 19.2; FP32 D2Q9+D2Q36
+// 64^2 9.9, 17.7, 512^2 (2048) 17.0, 19.7, but 768^2 (4608) 26.9, 25.2 and 1024^2
+// 51.1, 33.1: the low-order tiles hold the other set's LDS.  FP64 D2Q9+D2Q25
+// 512^2 (2048, where the CUs hold 256 at a time), a tenth high-order: 54, 35.
 template <typename S, bool TH, int NL, int NH>
 static int launch_pair(msl_ctx *c, int cur) {
   using P = SC2PairTraits<S, TH, NL, NH>;
@@ -251,7 +252,7 @@ static int launch_pair(msl_ctx *c, int cur) {
     const Geo &g = c->geo;
     const long long nlo = (long long)g.ntx * ((g.ny + P::TL::TY - 1) / P::TL::TY);
     const long long nhi = (long long)g.ntx * ((g.ny + P::TH_::TY - 1) / P::TH_::TY);
-    if (nlo + nhi > 2048) return MSL_ESTATE;
+    if (nlo + nhi > (P::WGS < 2 ? 1024 : 2048)) return MSL_ESTATE;
     auto run = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, dim3((unsigned)(nlo + nhi)), dim3(256), 0, c->stream, c->dtab, g,
                          (const S *)c->planes[0][cur], (S *)c->planes[0][cur ^ 1], (const S *)c->planes[1][cur],

@@ -730,6 +730,11 @@ struct SC2PairTraits {
   using TL = SC2Traits<S, TH, NL, SMALL>;
   using TH_ = SC2Traits<S, TH, NH>;
   static constexpr bool fits = TL::fits && TH_::fits;
+  using LL = SC2Lds<S, TH, NL, SMALL, NH>;
+  using LH = SC2Lds<S, TH, NH, false, NL>;
+  static constexpr int SM = LL::SM > LH::SM ? LL::SM : LH::SM, NTAB = LL::NTAB > LH::NTAB ? LL::NTAB : LH::NTAB;
+  // workgroups per CU by LDS
+  static constexpr int WGS = (160 * 1024) / (4 * SM + 8 * NTAB);
   // register budget: the tighter occupancy target of the two
   static constexpr int WAVES = TL::WAVES < TH_::WAVES ? TL::WAVES : TH_::WAVES;
 };
@@ -740,10 +745,8 @@ k_sc2d_pair(const Tab *__restrict__ tab, Geo g, const S *__restrict__ in_l, S *_
             const S *__restrict__ in_h, S *__restrict__ out_h, const uint8_t *__restrict__ cls,
             const uint8_t *__restrict__ tflag, int nlo, int faces) {
   using P = SC2PairTraits<S, TH, NL, NH>;
-  using LL = SC2Lds<S, TH, NL, P::SMALL, NH>;
-  using LH = SC2Lds<S, TH, NH, false, NL>;
-  __shared__ uint32_t sm[LL::SM > LH::SM ? LL::SM : LH::SM];
-  __shared__ double stab[LL::NTAB > LH::NTAB ? LL::NTAB : LH::NTAB];
+  __shared__ uint32_t sm[P::SM];
+  __shared__ double stab[P::NTAB];
   const int lin = (int)blockIdx.x;
   if (lin < nlo)
     sc2d_tile<S, TH, NL, P::SMALL, QE, NH>(tab, 0, g, in_l, out_l, cls, tflag, 0, out_h, faces, sm, stab, lin % g.ntx,
