@@ -529,10 +529,11 @@ def pond(args):
     periodic box of thermal D2Q16 (f and g, cv = 3/2, FP64): a smooth random
     flow (|u| <= 0.2, 5 % density and temperature variation) advected at
     (0.8, -0.3), tau 0.8, CFL 0.4.  The kernel is bound by FP64 arithmetic:
-    its roofline is the FP64 vector peak, with the algorithmic flops of the
-    reconstruction (per population, collocation point and pass: the two
-    one-axis transfer rows, 4 n (n - 1) flops, and the contraction and
-    weighting, 2 n^2 + 2 n + 2 flops for f and again for g) times the passes
+    its roofline is the FP64 vector peak, with the flops of the
+    reconstruction as the kernel shares them (per x node, collocation point and
+    pass: the point's x row over its n nodes, 2 n^2; for each of its n y nodes
+    the contraction over x nodes and the sums for the n target nodes, 4 n flops
+    for f and again for g, and the y row, 4 n + 2) times the passes
     the predictor-corrector took."""
     import numpy as np
     import torch
@@ -559,8 +560,8 @@ def pond(args):
     it_mean, it_max = s.pond_iterations()
     ncell = N * N
     Q = n * n
-    per_point = 4 * n * (n - 1) + (2 * n * n + 2 * n + 2) * (2 if th else 1)
-    flops = Q * 9 * per_point * it_mean * ncell          # per step
+    per_point = 2 * n * n + n * (4 * n * (2 if th else 1) + 4 * n + 2)
+    flops = n * 9 * per_point * it_mean * ncell          # per step
     achieved = flops / (ms / steps / 1e3) / 1e12
     out = {"metric": METRIC, "value": round(ncell * steps / (ms / 1e3) / 1e6, 2), "unit": "MLUPS",
            "n_gpus": 1, "steps": steps, "warmup": args.warmup, "ms_per_step": round(ms / steps, 5),
