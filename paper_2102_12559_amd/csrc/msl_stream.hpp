@@ -166,8 +166,17 @@ static int launch_one(msl_ctx *c, int lat, const char *in, char *out, char *oth)
         }
         return hipGetLastError() == hipSuccess ? MSL_OK : MSL_EHIP;
       };
-      if constexpr (sizeof(S) == 2) return walk(k_sc3d_zr<S, N, false>, k_sc3d_zr<S, N, true>, SC3RTraits<S, N>::NT);
-      else return walk(k_sc3d_zm<false>, k_sc3d_zm<true>, SC3ZTraits::NT);
+      // a slot on a fixed z face between y faces that map ghost rows: the stored
+      // slabs keep their own ghost rows
+      bool own = false;
+      for (int f = 4; f < 6; ++f) own |= c->cfg.bc[f] == MSL_BC_FIXED_EQ && c->cfg.slot[f][0] < c->cfg.slot[f][1];
+      own = own && ((c->faces >> 4) & 15);
+      auto run = [&]<bool OWN>() {
+        if constexpr (sizeof(S) == 2)
+          return walk(k_sc3d_zr<S, N, false, OWN>, k_sc3d_zr<S, N, true, OWN>, SC3RTraits<S, N>::NT);
+        else return walk(k_sc3d_zm<false, OWN>, k_sc3d_zm<true, OWN>, SC3ZTraits::NT);
+      };
+      return own ? run.template operator()<true>() : run.template operator()<false>();
     } else {
     // the other 3D sets (FP64, thermal, FP32 D3Q64): planes streamed through LDS
     // in chunks; the high-order set of a large grid runs over the compact list of
