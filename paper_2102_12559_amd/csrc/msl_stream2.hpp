@@ -165,9 +165,8 @@ __device__ __forceinline__ void sc2d_tile(const Tab *__restrict__ tab, int lat, 
   };
   // 1. every plane's window in flight at once (direct-to-LDS loads of 16-byte
   // chunks): voff holds a chunk's byte offset in a plane, without the plane's
-  // departure offset.  In tiles at a y end with faces to map (a uniform
-  // condition) a chunk has one row address for each of the three y origins.
-  auto issue = [&]<int K>(int soff, auto voff) {
+  // departure offset
+  auto issue = [&](int K, int soff, auto voff) {
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
         (void *)(in + (long long)K * g.plane), (short)0, (int)plane_b, MSL_RSRC_WORD3);
 #pragma unroll
@@ -184,20 +183,42 @@ __device__ __forceinline__ void sc2d_tile(const Tab *__restrict__ tab, int lat, 
     vrow[m] = d / CPR;
     vcol[m] = (d - vrow[m] * CPR) * 16u;
   }
+  // n0 + 1 of the nodes, two bits each
+  auto packed = [&](int ax) {
+    int v = 0;
+#pragma unroll
+    for (int a = 0; a < N; ++a) v |= (L.n0[ax][a] + 1) << (2 * a);
+    return v;
+  };
   if ((faces >> 4) && (y0 < MSL_G || y0 + TY + MSL_G > g.ny)) {
-    unsigned voff[3][M];
+    // tiles at a y end with faces to map (a uniform condition): a chunk has one
+    // row address for each of the three y origins (window rows start at
+    // y0 - 2 + o), chosen by value once per y node.  A loop over the y nodes: with
+    // every plane unrolled here as well, the table of addresses went to scratch
+    // where a window takes two loads per lane, with a wait for each load (65536 x 64
+    // D2Q9 FP64, a quarter of the tiles at an end: 211 us a step, 131 now).
+    unsigned v0[M], v1[M], v2[M];
 #pragma unroll
-    for (int m = 0; m < M; ++m)
+    for (int m = 0; m < M; ++m) {
+      auto at = [&](int o) { return (unsigned)(mapped(1, y0 - MSL_G + o + (int)vrow[m], g.ny) + MSL_G) * pitch_b + vcol[m]; };
+      v0[m] = at(0);
+      v1[m] = at(1);
+      v2[m] = at(2);
+    }
+    const int py = packed(1);
+#pragma unroll 1
+    for (int k = 0; k < NP / N; ++k) {
+      const int o = (py >> (2 * (k < N ? k : k - N))) & 3;
+      unsigned voff[M];
 #pragma unroll
-      for (int o = 0; o < 3; ++o)
-        voff[o][m] = (unsigned)(mapped(1, y0 - MSL_G + o + (int)vrow[m], g.ny) + MSL_G) * pitch_b + vcol[m];
-    msl_for_planes<NP>([&]<int K>() {
-      constexpr int i = K % Q, a = i % N, b = i / N;
-      const int o = L.n0[1][b] + 1;   // window rows start at y0 - 2 + o
-      issue.template operator()<K>((int)((unsigned)((g.xo + x0 + L.n0[0][a] - 1) * SZ) & ~3u), [&](int m) {
-        return o == 0 ? voff[0][m] : (o == 1 ? voff[1][m] : voff[2][m]);
-      });
-    });
+      for (int m = 0; m < M; ++m) {
+        const unsigned r0 = v0[m], r1 = v1[m], r2 = v2[m];
+        voff[m] = o == 0 ? r0 : (o == 1 ? r1 : r2);
+      }
+#pragma unroll
+      for (int a = 0; a < N; ++a)
+        issue(k * N + a, (int)((unsigned)((g.xo + x0 + L.n0[0][a] - 1) * SZ) & ~3u), [&](int m) { return voff[m]; });
+    }
   } else {
     unsigned voff[M];
 #pragma unroll
@@ -205,7 +226,7 @@ __device__ __forceinline__ void sc2d_tile(const Tab *__restrict__ tab, int lat, 
     msl_for_planes<NP>([&]<int K>() {
       constexpr int i = K % Q, a = i % N, b = i / N;
       const unsigned org = (unsigned)g.idx(x0 + L.n0[0][a] - 1, y0 + L.n0[1][b] - 1, 0) * SZ;   // window origin (bytes)
-      issue.template operator()<K>((int)(org & ~3u), [&](int m) { return voff[m]; });
+      issue(K, (int)(org & ~3u), [&](int m) { return voff[m]; });
     });
   }
   // band conversion tables of the other set, staged in LDS while the windows
@@ -232,29 +253,32 @@ __device__ __forceinline__ void sc2d_tile(const Tab *__restrict__ tab, int lat, 
       else if (t < NTAB) stab[t] = LO.isc[t - NO * N];
     }
   }
-  // my cells: inside the domain and of this velocity set; band: also
-  // converted into the other set
-  bool mine[R], band[R];
+  // my cells: the class byte, and the byte offset of the cell's store, beyond
+  // the plane outside the domain.  In FP32 and FP64 sets of 25 and 36 both stay
+  // in vector registers until the collision (the empty statements): as masks,
+  // and with the grid's strides, they would hold scalar registers through the
+  // reconstruction, whose tables need them all, and the LDS reads lose their
+  // overlap (1000^2 FP32 D2Q36, fixed faces: 87.0 us a step without, 78.0 with;
+  // 16-bit sets, whose registers are short, lose: D2Q36 thermal 137.5, 174.9).
+  constexpr bool HOLD = SZ >= 4 && N >= 5;
+  unsigned soff_cell[R], cb[R], lat_v = (unsigned)lat;
+  if (HOLD) asm volatile("" : "+v"(lat_v));
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int x = x0 + tx, y = y0 + ty * R + r;
     const bool inside = x < g.nx && y < g.ny;
-    const uint8_t cb = cls[inside ? (long long)y * g.nx + x : 0];
-    mine[r] = inside && (cb & 1) == lat;
-    band[r] = NO > 0 && mine[r] && (cb & 2);
+    cb[r] = cls[inside ? (long long)y * g.nx + x : 0];
+    soff_cell[r] = inside ? (unsigned)g.idx(x, y, 0) * SZ : 0x80000000u;
+    if (HOLD) asm volatile("" : "+v"(soff_cell[r]));
   }
   // tiles at an x end (a uniform condition): the ghost columns X = -2, -1, nx,
   // nx + 1 of every window row inside the domain, read while the windows load
-  if ((faces & 15) && (x0 < MSL_G || x0 + MSL_TX + MSL_G > g.nx)) {
-    constexpr int NG = NP * LR * 2 * MSL_G, NIT = (NG + 255) / 256;
-    S val[NIT];
-    int dst[NIT];   // LDS byte, -1: nothing to replace
-    int nx0 = 0, ny0 = 0;   // n0 + 1 of the nodes, two bits each
-#pragma unroll
-    for (int a = 0; a < N; ++a) {
-      nx0 |= (L.n0[0][a] + 1) << (2 * a);
-      ny0 |= (L.n0[1][a] + 1) << (2 * a);
-    }
+  constexpr int NG = NP * LR * 2 * MSL_G, NIT = (NG + 255) / 256;
+  S val[NIT];
+  int dst[NIT];   // LDS byte, -1: nothing to replace
+  const bool xend = (faces & 15) && (x0 < MSL_G || x0 + MSL_TX + MSL_G > g.nx);
+  if (xend) {
+    const int nx0 = packed(0), ny0 = packed(1);
 #pragma unroll
     for (int n = 0; n < NIT; ++n) {
       const int it = threadIdx.x + 256 * n;
@@ -270,12 +294,14 @@ __device__ __forceinline__ void sc2d_tile(const Tab *__restrict__ tab, int lat, 
         }
       }
     }
-    __syncthreads();   // the compiler waits for the loads before the barrier
+  }
+  __syncthreads();   // the compiler waits for the loads before the barrier
+  if (xend) {
 #pragma unroll
     for (int n = 0; n < NIT; ++n)
       if (dst[n] >= 0) *(S *)((char *)sm + dst[n]) = val[n];
+    __syncthreads();
   }
-  __syncthreads();
 
   // reconstruction of plane K at this thread's R cells (raw storage domain)
   auto recon = [&]<int K>(C (&ft)[R]) {
@@ -431,13 +457,18 @@ __device__ __forceinline__ void sc2d_tile(const Tab *__restrict__ tab, int lat, 
   double acc[PROJ ? (TH ? 2 : 1) * QO : 1][R];   // (P x P) f per output node
   double tp[PROJ ? NO : 1][R];                   // P along x of the current row
   double Pp[PROJ ? NO : 1][PROJ ? N : 1];        // P[a'][a], from LDS
-  bool wband = false;
-  if constexpr (NO > 0) {
-    bool b = false;
+  // this velocity set's cells inside the domain; band cells (band_bits: bit r)
+  // are also converted into the other set
+  unsigned band_bits = 0;
 #pragma unroll
-    for (int r = 0; r < R; ++r) b |= band[r];
-    wband = __any(b);
+  for (int r = 0; r < R; ++r) {
+    if (HOLD) asm volatile("" : "+v"(cb[r]));
+    const bool mine = (cb[r] & 1) == lat_v;
+    if (NO > 0) band_bits |= mine && (cb[r] & 2) && soff_cell[r] < 0x80000000u ? 1u << r : 0u;
+    soff_cell[r] = mine ? soff_cell[r] : 0x80000000u;
   }
+  auto band = [&](int r) { return ((band_bits >> r) & 1u) != 0; };
+  const bool wband = NO > 0 && __any(band_bits != 0);
   if constexpr (PROJ) {
 #pragma unroll
     for (int k = 0; k < (TH ? 2 : 1) * QO; ++k)
@@ -455,12 +486,6 @@ __device__ __forceinline__ void sc2d_tile(const Tab *__restrict__ tab, int lat, 
     }
   }
   // 4. collide and store
-  unsigned soff_cell[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int x = x0 + tx, y = y0 + ty * R + r;
-    soff_cell[r] = mine[r] ? (unsigned)g.idx(x, y, 0) * SZ : 0x80000000u;
-  }
   auto pass2 = [&]<int K>() {
     constexpr int i = K % Q, a = i % N, b = i / N;
     const C W = tsel<C>(L.sc[i], L.scf[i]);
@@ -531,15 +556,14 @@ __device__ __forceinline__ void sc2d_tile(const Tab *__restrict__ tab, int lat, 
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         if constexpr (LIFT) {
-          if (!__ballot(band[r])) continue;
+          if (!__ballot(band(r))) continue;
         } else {
-          if (!band[r]) continue;
+          if (!band(r)) continue;
         }
         // buffer stores: the plane's base in scalar registers, one 32-bit
         // byte offset per lane (a 64-bit address per store would not fit in
         // the registers of an eight-wave launch)
-        const int cidx = (int)g.idx(x0 + tx, y0 + ty * R + r, 0);
-        const int boff = (int)((unsigned)cidx * SZ);
+        const int boff = (int)soff_cell[r], cidx = (int)(soff_cell[r] / SZ);
         auto put = [&](const int k, const double v, const double is) {
           const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
               (void *)(oth + (long long)k * g.plane), (short)0, (int)plane_b, MSL_RSRC_WORD3);
@@ -560,7 +584,7 @@ __device__ __forceinline__ void sc2d_tile(const Tab *__restrict__ tab, int lat, 
           if (TH) Tm = ((double)en[r] - 0.5 * rd * (ux * ux + uy * uy)) / (tab->cv * rd);
           const double tm1 = Tm * LO.iTr - 1.0;
           const double uxs = (ux - LO.ur[0]) * LO.isq, uys = (uy - LO.ur[1]) * LO.isq;
-          unsigned long long bmask = __ballot(band[r]);
+          unsigned long long bmask = __ballot(band(r));
           if (__popcll(bmask) <= MSL_LIFT_COOP) {
             // few band cells in the wave: the wave lifts them one at a time,
             // lane i computing output node i (its Hermite factors and the
@@ -610,7 +634,7 @@ __device__ __forceinline__ void sc2d_tile(const Tab *__restrict__ tab, int lat, 
             }
             continue;
           }
-          if (!band[r]) continue;
+          if (!band(r)) continue;
           // many band cells: each lane lifts its own.  Equilibrium factors
           // of the high-order nodes (eq_axis with the basis from LDS): all of
           // y here, x per output column below (its Hermite coefficients
