@@ -274,7 +274,9 @@ k_pond_step(const Tab *__restrict__ tab, int lat, const uint8_t *__restrict__ cl
 #pragma unroll 1
       for (int sr = -2; sr <= 2; ++sr) {
         // the y weights of this row of points for every node b (zero outside
-        // its stencil); rows that no lane of the wave needs are left out
+        // its stencil); a cell leaves out the rows that none of its nodes needs,
+        // also where another cell of the wave needs them: their weights are zero,
+        // but a point without a finite state would reach the cell all the same
         bool use = false;
         double wy[N];
 #pragma unroll
@@ -285,7 +287,7 @@ k_pond_step(const Tab *__restrict__ tab, int lat, const uint8_t *__restrict__ cl
           use |= in;
           wy[b] = in ? (s == 0 ? w0 : w1) : 0.0;
         }
-        if (!__any(use)) continue;
+        if (!use) continue;
         double vf[N], vg[TH ? N : 1];
 #pragma unroll
         for (int b = 0; b < N; ++b) {
@@ -948,9 +950,11 @@ template <bool TH, bool QE>
 static int pond_step_th(msl_ctx *c, int lat) {
   // Point columns on lanes of their own: N = 5 always (the two-set shock's
   // D2Q25 launch 94 us without, 45 us with); N = 3, 4 while the plain layout's
-  // 64-cell workgroups leave three CUs in four idle (12 or 9 of 16 lanes work:
-  // thermal D2Q16 at 144 workgroups 36.6 us a step with, 35.1 without; at 650
-  // 89 against 61); N = 6 has no room for them in 16 lanes.
+  // 64-cell workgroups leave three CUs in four idle (12 or 9 of 16 lanes work).
+  // us a step, with against without: thermal D2Q16 15.3, 21.5 at 4 workgroups
+  // (16 x 16), 16.8, 24.4 at 64 (64 x 64), 36.6, 35.1 at 144, 89, 61 at 650;
+  // athermal D2Q9 10.9, 12.0 and 11.3, 12.4 at 4 and 64.  N = 6 has no room for
+  // them in 16 lanes.
   const long long wgs = (long long)((c->geo.nx + 15) / 16) * ((c->geo.ny + 3) / 4);
   const bool spx = wgs <= 64;
   switch (c->htab.lat[lat].n) {
