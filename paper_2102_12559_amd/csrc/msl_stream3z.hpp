@@ -64,14 +64,6 @@ __device__ __forceinline__ void msl_lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// 1 / v to FP64 rounding (v normal and finite): the hardware's estimate and two
-// Newton steps, a shorter dependent chain than the IEEE division
-__device__ __forceinline__ double msl_rcp(double v) {
-  double r = __builtin_amdgcn_rcp(v);
-  r = __builtin_fma(__builtin_fma(-v, r, 1.0), r, r);
-  return __builtin_fma(__builtin_fma(-v, r, 1.0), r, r);
-}
-
 // a 16-bit stored element (the low 16 bits of u) as float
 template <typename S>
 __device__ __forceinline__ float half_elem(uint32_t u);
@@ -371,7 +363,7 @@ k_sc3d_zm(const Tab *__restrict__ tab, int lat, Geo g, const float *__restrict__
         // equilibrium factors in FP64 (no rounding bias in the equilibrium's
         // mass and momentum), kept in the compute precision; athermal: T = 1
         const double rd = (double)rho, dx = (double)jx, dy = (double)jy, dz = (double)jz;
-        const double ird = msl_rcp(rd);
+        const double ird = 1.0 / rd;
         C om = tp->omegaf;
         if (tp->tau_mode == 1) om = (C)(1.0 / (tp->mu_T1 / (rd * tp->dt) + 0.5));
         double p[N];
