@@ -8,12 +8,6 @@ template <typename C> __device__ __forceinline__ C tsel(double d, float f);
 template <> __device__ __forceinline__ double tsel<double>(double d, float) { return d; }
 template <> __device__ __forceinline__ float tsel<float>(double, float f) { return f; }
 
-// Register budget heuristic: cells per thread along the marching axis so that
-// the interpolated populations of all planes fit in about `budget` VGPRs.
-__host__ __device__ constexpr int msl_rows_for(int nplanes, int words, int budget) {
-  return budget / (nplanes * words) >= 4 ? 4 : (budget / (nplanes * words) >= 2 ? 2 : 1);
-}
-
 // 1D factor of the lattice equilibrium: the populations w_a P(c_a) whose first
 // n moments are those of a Gaussian with mean u and variance theta.  With
 // Gauss-Hermite orthogonality P(c) = sum_{j<n} He_j(c) b_j / j!, where

@@ -437,7 +437,7 @@ k_mlp_train(const float *__restrict__ prm, int F, int O, const float *__restrict
   __syncthreads();
   // bias gradients: a column's sum over the rows of the tile
   auto colsum = [&](float *gb, int col, float cs) {
-    cs = 0.f + cs;
+    cs = 0.f + cs;   // a sum that starts from zero: never -0
     cs += __shfl_xor(cs, 16);
     cs += __shfl_xor(cs, 32);
     if (lg == 0) gb[col] = cs;

@@ -1,23 +1,14 @@
-// msl_stream.hpp -- the fused stream-and-collide kernel, one instantiation per
-// (dimension, velocity-set order, storage precision, thermal model).
-//
-// This file holds the register-staged 2D kernel used where the LDS-resident
-// one (msl_stream2.hpp) does not fit, and the launcher; 3D runs use the
-// chunked kernel of msl_stream3.hpp.
-//
-// One workgroup owns a tile of 64 x TY cells.
-// For each population plane (f_0..f_{Q-1}, then g_0..g_{Q-1}) the workgroup
-// stages the plane's (64+2) x (TY+2) neighbourhood of the departure points into
-// LDS -- the departure offset x - c_i dt is the same for every cell of a plane,
-// so the staged window is the tile shifted by the population's base offset --
-// while the next plane's global loads are in flight (double-buffered LDS, one
-// barrier per plane).  Each thread interpolates its cells separably (rows,
-// then columns; eq. reconstructionPond with 3-point Lagrange functions) into
-// registers.  After the last plane every cell holds all its streamed
-// populations and is collided in registers: moments, Hermite product-form
-// equilibrium, BGK (eqs. Pond_f/g, omega1 = omega2), and stored coalesced.
-// Cells of the other velocity set are skipped; tiles without a cell of this
-// set exit before loading anything.
+// msl_stream.hpp -- dispatch of the fused stream-and-collide launches, by
+// dimension, velocity-set order, storage precision and thermal model:
+//   2D  every plane's window resident in LDS (msl_stream2.hpp), which also
+//       converts the band cells of two-set runs, both sets in one launch on small
+//       grids; thermal FP64 D2Q25 and D2Q36, whose windows do not fit, a wave per
+//       x node (msl_stream2s.hpp)
+//   3D  column walks along z for athermal 16-bit storage and FP32 D3Q27
+//       (msl_stream3z.hpp); planes streamed through LDS in chunks otherwise
+//       (msl_stream3.hpp)
+// Cells of the other velocity set are skipped; tiles without a cell of this set
+// exit before loading anything.
 #pragma once
 #include <utility>
 
@@ -144,25 +135,33 @@ static int launch_one(msl_ctx *c, int lat, const char *in, char *out, char *oth)
       const long long cols = (long long)g.ntx * g.nty;
       const int zc = cols * ((g.nz + 7) / 8) >= 256 ? MSL_WALK_ZC : 4;
       const int ncz = (g.nz + zc - 1) / zc;
-      auto walk = [&](auto dense, auto list, int nt) -> int {
-        if (lat != 0 && cols * ncz > MSL_WALK_LIST_MIN) {
-          if (c->capturing) return MSL_ESTATE;   // the list length is read by the host
-          if (!c->tl_ok) {
-            if (msl_launch_tile_list(c, lat, 1, zc)) return MSL_EHIP;
-            int n = 0;
-            if (hipMemcpyAsync(&n, c->tcount, sizeof(int), hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
-                hipStreamSynchronize(c->stream) != hipSuccess)
-              return MSL_EHIP;
-            c->tl_n = n;
-            c->tl_ok = 1;
-          }
-          if (c->tl_n == 0) return MSL_OK;
-          hipLaunchKernelGGL(list, dim3((unsigned)c->tl_n), dim3(nt), 0, c->stream, c->dtab, lat, g, (const S *)in,
-                             (S *)out, c->cls, c->tflag, 0, c->xmir, c->faces, zc, c->tlist, c->tcount);
+      const dim3 grid((g.nx + MSL_TX - 1) / MSL_TX, (g.ny + MSL_MTY - 1) / MSL_MTY, ncz);
+      auto walk = [&]<bool OWN>() -> int {
+        if constexpr (sizeof(S) == 4) {
+          hipLaunchKernelGGL((k_sc3d_zm<OWN>), grid, dim3(SC3ZTraits::NT), 0, c->stream, c->dtab, lat, g, (const S *)in,
+                             (S *)out, c->cls, c->tflag, lat == 0, c->xmir, c->faces, zc);
         } else {
-          dim3 grid((g.nx + MSL_TX - 1) / MSL_TX, (g.ny + MSL_MTY - 1) / MSL_MTY, ncz);
-          hipLaunchKernelGGL(dense, grid, dim3(nt), 0, c->stream, c->dtab, lat, g, (const S *)in, (S *)out, c->cls,
-                             c->tflag, lat == 0, c->xmir, c->faces, zc, (const int *)nullptr, (const int *)nullptr);
+          const dim3 nt(SC3RTraits<S, N>::NT);
+          if constexpr (N > 3) {
+            if (lat != 0 && cols * ncz > MSL_WALK_LIST_MIN) {
+              if (c->capturing) return MSL_ESTATE;   // the list length is read by the host
+              if (!c->tl_ok) {
+                if (msl_launch_tile_list(c, lat, 1, zc)) return MSL_EHIP;
+                int n = 0;
+                if (hipMemcpyAsync(&n, c->tcount, sizeof(int), hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
+                    hipStreamSynchronize(c->stream) != hipSuccess)
+                  return MSL_EHIP;
+                c->tl_n = n;
+                c->tl_ok = 1;
+              }
+              if (c->tl_n == 0) return MSL_OK;
+              hipLaunchKernelGGL((k_sc3d_zr<S, N, true, OWN>), dim3((unsigned)c->tl_n), nt, 0, c->stream, c->dtab, lat, g,
+                                 (const S *)in, (S *)out, c->cls, c->tflag, 0, c->xmir, c->faces, zc, c->tlist, c->tcount);
+              return hipGetLastError() == hipSuccess ? MSL_OK : MSL_EHIP;
+            }
+          }
+          hipLaunchKernelGGL((k_sc3d_zr<S, N, false, OWN>), grid, nt, 0, c->stream, c->dtab, lat, g, (const S *)in, (S *)out,
+                             c->cls, c->tflag, lat == 0, c->xmir, c->faces, zc, (const int *)nullptr, (const int *)nullptr);
         }
         return hipGetLastError() == hipSuccess ? MSL_OK : MSL_EHIP;
       };
@@ -170,21 +169,15 @@ static int launch_one(msl_ctx *c, int lat, const char *in, char *out, char *oth)
       // slabs keep their own ghost rows
       bool own = false;
       for (int f = 4; f < 6; ++f) own |= c->cfg.bc[f] == MSL_BC_FIXED_EQ && c->cfg.slot[f][0] < c->cfg.slot[f][1];
-      own = own && ((c->faces >> 4) & 15);
-      auto run = [&]<bool OWN>() {
-        if constexpr (sizeof(S) == 2)
-          return walk(k_sc3d_zr<S, N, false, OWN>, k_sc3d_zr<S, N, true, OWN>, SC3RTraits<S, N>::NT);
-        else return walk(k_sc3d_zm<false, OWN>, k_sc3d_zm<true, OWN>, SC3ZTraits::NT);
-      };
-      return own ? run.template operator()<true>() : run.template operator()<false>();
+      return own && ((c->faces >> 4) & 15) ? walk.template operator()<true>() : walk.template operator()<false>();
     } else {
     // the other 3D sets (FP64, thermal, FP32 D3Q64): planes streamed through LDS
     // in chunks; the high-order set of a large grid runs over the compact list of
     // its live tiles (as in 2D)
     using T3 = SC3Traits<S, TH, N>;
-    const long long tiles = (long long)g.ntx * g.nty * ((g.ntz + T3::RZ - 1) / T3::RZ);
-    const long long fit = 256LL * ((160 * 1024) / T3::LDS_BYTES);
-    {
+    if constexpr (N > 3) {
+      const long long tiles = (long long)g.ntx * g.nty * ((g.ntz + T3::RZ - 1) / T3::RZ);
+      const long long fit = 256LL * ((160 * 1024) / T3::LDS_BYTES);
       if (lat != 0 && tiles > 4 * fit) {
         if (c->capturing) return MSL_ESTATE;   // the list length is read by the host
         if (!c->tl_ok) {
@@ -253,7 +246,11 @@ int msl_launch_store_th(msl_ctx *c, int lat, const char *in, char *out, char *ot
 // 6.4, 12.8, 256^2 7.3, 12.2, 512^2 (1536 workgroups) 16.4, 19.2; FP32 D2Q9+D2Q36
 // 64^2 9.9, 17.7, 512^2 (2048) 17.0, 19.7, but 768^2 (4608) 26.9, 25.2 and 1024^2
 // 51.1, 33.1: the low-order tiles hold the other set's LDS.  FP64 D2Q9+D2Q25
-// 512^2 (2048, where the CUs hold 256 at a time), a tenth high-order: 54, 35.
+// 512^2 (2048, where the CUs hold 256 at a time), a tenth high-order: 54, 35.  Up
+// to 1024 workgroups one launch wins in that class too: D2Q9+D2Q25 256^2 (512)
+// 13.2, 15.5, 320^2 (800) 14.4, 16.2; the closest of its pairs, thermal FP64
+// D2Q9+D2Q16, 320^2 19.2, 20.7 (a sixteenth of the grid high-order; half: 1.17 to
+// 1.6 times).
 template <typename S, bool TH, int NL, int NH>
 static int launch_pair(msl_ctx *c, int cur) {
   using P = SC2PairTraits<S, TH, NL, NH>;

@@ -1,8 +1,8 @@
 // msl_stream3.hpp -- the 3D stream-and-collide kernel: population planes
 // streamed through LDS in chunks, the reconstructed values held in registers.
 //
-// A workgroup owns 64 x 4 x RZ cells, RZ cells per lane along z (2 for D3Q27,
-// 1 for D3Q64).  The planes
+// A workgroup owns 64 x 4 x RZ cells, RZ cells per lane along z (2 for D3Q27, 1
+// with g in FP64; 1 for D3Q64, 2 in athermal FP32).  The planes
 // (f_0..f_{Q-1}, then g_0..g_{Q-1}) are taken CH at a time: direct-to-LDS
 // buffer loads of every plane's 66 x 6 x (RZ + 2) window around the departure points
 // of the tile (the departure offset x - c_i dt is the same for every cell of a

@@ -79,7 +79,7 @@ __device__ __forceinline__ float half_elem(uint32_t) { return 0.0f; }
 // columns of the high-order set beyond which its launch runs over the list of
 // live columns: 32 per CU, of which a criterion's set fills a part
 #define MSL_WALK_LIST_MIN 8192
-#define MSL_WALK_ZC 8   // most cells of a column along z (bits of a 32-bit word per lane)
+#define MSL_WALK_ZC 8   // most cells of a column along z
 
 struct SC3ZTraits {
   static constexpr int N = 3, Q = N * N * N;
@@ -108,12 +108,11 @@ struct SC3ZTraits {
 // otherwise a stored slab is uniform or follows the y faces' rules, and its rows
 // are mapped like every other slab's.  A variant of its own: the choice inside
 // the walk cost 1 to 4 % of every run (16-bit D3Q27 64^3 30.1 us a step, 31.1).
-template <bool LIST, bool OWN>
+template <bool OWN>
 __global__ void __launch_bounds__(SC3ZTraits::NT) __attribute__((amdgpu_waves_per_eu(SC3ZTraits::WAVES)))
 k_sc3d_zm(const Tab *__restrict__ tab, int lat, Geo g, const float *__restrict__ in,
           float *__restrict__ out, const uint8_t *__restrict__ cls,
-          const uint8_t *__restrict__ tflag, int remap, int xmir, int faces, int zc, const int *__restrict__ tlist,
-          const int *__restrict__ tcount) {
+          const uint8_t *__restrict__ tflag, int remap, int xmir, int faces, int zc) {
   using Tr = SC3ZTraits;
   typedef float C;
   constexpr int N = Tr::N, Q = Tr::Q, NWV = Tr::NWV, PW = Tr::PW, R = Tr::R, M = Tr::M;
@@ -122,17 +121,9 @@ k_sc3d_zm(const Tab *__restrict__ tab, int lat, Geo g, const float *__restrict__
   __shared__ float s_part[(NWV - 1) * NPS][256];   // partial moments of the waves that do not own the row
   __shared__ float s_fac[Tr::NFAC][256];           // equilibrium factors per axis (x with rho), omega
   const LatTab &L = tab->lat[lat];
-  // the column: from the grid (XCD-aware order for dense launches), or one
-  // workgroup per entry of the compact list of live columns (sparse launches)
-  int tile;
-  if constexpr (LIST) {
-    const int n = *tcount;
-    if ((int)blockIdx.x >= n) return;
-    tile = tlist[msl_xcd_tile((int)blockIdx.x, n)];
-  } else {
-    const int lin = (int)((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x);
-    tile = remap ? msl_xcd_tile(lin, (int)(gridDim.x * gridDim.y * gridDim.z)) : lin;
-  }
+  // the column (XCD-aware order; the low-order set's launches are dense)
+  const int lin = (int)((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x);
+  const int tile = remap ? msl_xcd_tile(lin, (int)(gridDim.x * gridDim.y * gridDim.z)) : lin;
   const int bx = tile % g.ntx, by = (tile / g.ntx) % g.nty;
   const int z0 = tile / (g.ntx * g.nty) * zc;
   const int x0 = bx * MSL_TX, y0 = by * MSL_MTY;
@@ -149,23 +140,23 @@ k_sc3d_zm(const Tab *__restrict__ tab, int lat, Geo g, const float *__restrict__
   const unsigned plane_b = (unsigned)g.plane * SZ;
   const unsigned slab_b = (unsigned)g.rows * pitch_b;
   // the cells of this velocity set along the column, as bits per cell (bit k:
-  // z0 + k): 8 z cells per thread, through LDS
+  // z0 + k), through LDS
   uint32_t mine[R];
   {
+    static_assert(MSL_WALK_ZC <= 8, "a byte per cell of the cross-section");
     uint8_t *bits = (uint8_t *)s_fac;
-    for (int e = threadIdx.x; e < 1024; e += Tr::NT) {
-      const int q = e >> 8, ci = e & 255, x = x0 + (ci & 63), y = y0 + (ci >> 6);
+    if (threadIdx.x < 256) {
+      const int x = x0 + (threadIdx.x & 63), y = y0 + (threadIdx.x >> 6);
       unsigned m = 0;
       if (x < g.nx && y < g.ny)
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-          if (8 * q + j < zn)
-            m |= (unsigned)((cls[((long long)(z0 + 8 * q + j) * g.ny + y) * g.nx + x] & 1) == lat) << j;
-      bits[4 * ci + q] = (uint8_t)m;
+        for (int j = 0; j < MSL_WALK_ZC; ++j)
+          if (j < zn) m |= (unsigned)((cls[((long long)(z0 + j) * g.ny + y) * g.nx + x] & 1) == lat) << j;
+      bits[threadIdx.x] = (uint8_t)m;
     }
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < R; ++r) mine[r] = ((const uint32_t *)bits)[64 * r + lane];
+    for (int r = 0; r < R; ++r) mine[r] = bits[64 * r + lane];
   }
   // interpolation weights and window offsets of the departure stencil
   C wx[3][N], wy[3], wz[3];
