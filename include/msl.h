@@ -311,6 +311,12 @@ int msl_profile(msl_ctx *ctx, int every);
  * population of each cell of that order), cells updated.  Host out, 24
  * doubles; the counters restart.  Synchronises. */
 int msl_profile_read(msl_ctx *ctx, double *stats);
+
+/* Steps so far whose two velocity sets went in one launch (small two-set 2D
+ * grids; a step captured into a step graph counts once).  Steps timed by
+ * msl_profile launch the sets apart, with the same results, so that its classes
+ * keep their meaning: on such grids their sum is longer than an untimed step. */
+int msl_paired_steps(const msl_ctx *ctx, long *steps);
 /* Plain device-to-device copy of `bytes` (a multiple of 16) on `hip_stream`:
  * the bandwidth reference for roofline figures.  Device pointers. */
 int msl_device_copy(void *dst, const void *src, size_t bytes, void *hip_stream);

@@ -613,6 +613,12 @@ int msl_get_step(const msl_ctx *c, long *step) {
   return MSL_OK;
 }
 
+int msl_paired_steps(const msl_ctx *c, long *steps) {
+  if (!c || !steps) return MSL_EINVAL;
+  *steps = c->npair;
+  return MSL_OK;
+}
+
 static int refresh_band(msl_ctx *c) {
   int rc = msl_launch_classify(c);
   if (rc) return rc;
@@ -845,6 +851,7 @@ static int plain_step(msl_ctx *c, bool fork) {
     rc = msl_launch_stream_pair(c, cur);
     if (rc != MSL_OK && rc != MSL_ESTATE) { set_err(c, "stream-collide launch failed"); return rc; }
     paired = rc == MSL_OK;
+    c->npair += paired;
   }
   fork = fork && c->nlat > 1 && !paired;
   if (fork) {

@@ -213,8 +213,9 @@ struct msl_ctx {
   // (paths that need the host inside a step refuse it).
   int gmode, gB, capturing;
   // the stream-collide launches convert the band cells themselves (no band
-  // conversion launch in a step)
+  // conversion launch in a step); npair: steps that took both sets in one launch
   int fuse;
+  long npair;
   hipStream_t gs[2];
   hipEvent_t gev[2];
   hipGraphExec_t gx[2];

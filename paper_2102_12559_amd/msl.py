@@ -58,7 +58,7 @@ SYMBOLS = [
     "msl_set_state", "msl_mlp_dims", "msl_collect_snapshots", "msl_mlp_set_weights",
     "msl_mlp_get_weights", "msl_mlp_train", "msl_mlp_grad", "msl_mlp_forward",
     "msl_mlp_get_flags", "msl_mlp_set_flags", "msl_num_check_tiles", "msl_profile",
-    "msl_profile_read", "msl_device_copy", "msl_mlp_grad_noalloc", "msl_error_norms",
+    "msl_profile_read", "msl_paired_steps", "msl_device_copy", "msl_mlp_grad_noalloc", "msl_error_norms",
     "msl_pond_frames", "msl_pond_iterations", "msl_set_graph",
 ]
 
@@ -315,6 +315,13 @@ class Solver:
     def profile(self, enable=True, every=1):
         """Time the launches of every `every`-th step (HIP events)."""
         self._check(lib().msl_profile(self._ctx, int(every) if enable else 0), "msl_profile")
+
+    @property
+    def paired_steps(self):
+        """Steps so far whose two velocity sets went in one launch (msl_paired_steps)."""
+        n = C.c_long()
+        self._check(lib().msl_paired_steps(self._ctx, C.byref(n)), "msl_paired_steps")
+        return n.value
 
     def profile_read(self):
         st = (C.c_double * 24)()
