@@ -124,10 +124,6 @@ static void build_lat(LatTab &L, int n, int dim, const ld *x, const ld *w, doubl
     L.cr[a] = (double)x[a];
     L.w[a] = (double)w[a];
     L.wf[a] = (float)w[a];
-    ld den = 1.0L;
-    for (int b = 0; b < n; ++b)
-      if (b != a) den *= x[a] - x[b];
-    L.den[a] = (double)(1.0L / den);
     ld fact = 1.0L;
     for (int j = 0; j < n; ++j) {
       if (j > 0) fact *= (ld)j;
@@ -422,6 +418,8 @@ int msl_create(const msl_config *cfg, void *ws, size_t bytes, void *stream, msl_
   const double rho0 = cfg->rho0 > 0 ? cfg->rho0 : 1.0, T0 = cfg->T0 > 0 ? cfg->T0 : 1.0;
   for (int l = 0; l < c->nlat; ++l)
     build_lat(t.lat[l], ns[l], cfg->dim, xs[l], wsl[l], dt, ur, Tref, su, rho0, T0);
+  if (cfg->pond)
+    for (int l = 0; l < c->nlat; ++l) msl_pond_tables(t.lat[l]);
   for (int l = 0; l < c->nlat; ++l)
     for (int ax = 0; ax < cfg->dim; ++ax)
       for (int a = 0; a < ns[l]; ++a)

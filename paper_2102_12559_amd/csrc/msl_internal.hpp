@@ -27,7 +27,7 @@
 struct LatTab {
   int n, Q;
   double cr[MSL_MAXN], w[MSL_MAXN];
-  double den[MSL_MAXN];            // 1 / prod_{b != a} (c_a - c_b)
+  double den[MSL_MAXN], deny[MSL_MAXN];   // co-moving step: 1 / prod_{b != a} (c_a - c_b), x and y
   double hw[MSL_MAXN][MSL_MAXN];   // w_a He_j(c_a) / j!
   double v[3][MSL_MAXN];           // particle velocity of node a along axis
   int n0[3][MSL_MAXN];
@@ -244,6 +244,7 @@ int msl_pond_launch_init(msl_ctx *c, const double *rho, const double *u, const d
 int msl_pond_launch_macros(msl_ctx *c, double *rho, double *u, double *T);
 int msl_pond_launch_step(msl_ctx *c);
 int msl_pond_launch_stats(msl_ctx *c);
+void msl_pond_tables(LatTab &L);   // its denominators of the step
 #define MSL_POND_SLOT_X 4   // cells of the narrowest step workgroup along x and y
 #define MSL_POND_SLOT_Y 4
 // co-moving frames, two sets: cells whose set differs from `mask` convert their
