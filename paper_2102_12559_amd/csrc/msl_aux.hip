@@ -191,7 +191,7 @@ k_bc_fixed(const Tab *__restrict__ tab, Geo g, int ax, BCArgs b, char *bl, char 
 // columns: 16 threads of each share out the arriving populations of the
 // adjacent cell (their sums meet in LDS) and then the planes of both sets, in
 // both ghost layers.  One thread per ghost cell, its populations one after the
-// other, took 22 us on an 8 x 64 channel, all of it latency; this 2 to 3 us.
+// other, took 22 us on an 8 x 64 channel, all of it latency; this 4.6 us.
 #define DIFF_COLS 16
 template <typename S>
 __global__ void __launch_bounds__(AUX_BLOCK)

@@ -139,9 +139,9 @@ __device__ __forceinline__ long long pond_resolve(const PondArgs &pa, int x, int
   return (long long)y * pa.nx + x;
 }
 
-// Bound by FP64 issue (the VALU issues about 70 % of the time).  A step of
+// Bound by FP64 issue (the VALU issues about 80 % of the time).  A step of
 // 1024^2 thermal D2Q16, 3 passes: 6.7 ms with one lane per population and
-// pass counts by atomics, 0.80 ms now; 512^2: 1692 us, 225 us now (432 us with
+// pass counts by atomics, 0.78 ms now; 512^2: 1692 us, 225 us now (432 us with
 // the atomics).  The 4096 x 4 two-set shock, bound by latency: 139 and 122 us
 // for its D2Q16 and D2Q25 launches, 29 and 45 us now.
 template <int N, bool TH, bool QE, bool SPX>
